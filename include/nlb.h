@@ -339,8 +339,8 @@ int nlb_rnn_update(nlb_table *h, const int32_t *src, const int32_t *dst, const u
  * memory with hipMemset: its working memory -- the winner word of each of
  * the table's N nodes (8 B), a list of 16 B per pair row, the GRU weights
  * repacked in matrix-operand fragments (3 KiB per 16 status columns and
- * 32 input columns of w_ih and w_hh together), and 2 n candidate status
- * rows -- lives in one static device array of NLB_NOALLOC_SCRATCH bytes per
+ * 32 input columns of w_ih and w_hh together), and 2 n staged status rows
+ * -- lives in one static device array of NLB_NOALLOC_SCRATCH bytes per
  * device, which the library holds until the process ends.  The call needs
  * align256(8 N) + align256(16 (2 n) + 256) + align256(3072 (pad32(d) / 16)
  * ((k_x + pad32(d)) / 32)) + 2 n * status row bytes of it (k_x: the row

@@ -598,8 +598,6 @@ __device__ __forceinline__ void piece_operand(const Piece8<KIND> &r, uint32_t di
     }
 }
 
-typedef float f32x4_at4 __attribute__((ext_vector_type(4), aligned(4)));
-
 // MLP_out for a group of up to 16 queries: row r16 = query qb + r16, input
 // [r_u | aggregate], the aggregate w2 aggd + b2 (zero for a query without
 // valid rows, ne = 0); aggd[a] holds head a's finished aggregates
@@ -1699,8 +1697,6 @@ __device__ __forceinline__ uint32_t opaque_u32(uint32_t x) {
     asm volatile("" : "+s"(x));
     return x;
 }
-
-typedef uint32_t u32x4_at4 __attribute__((ext_vector_type(4), aligned(4)));
 
 struct GroupParams : RowParams {
     uint32_t k1, off_e, off_t, k3;   // row widths of w1 / w3, first columns of the link rows and of the encoding in w1

@@ -711,7 +711,7 @@ int nlb_destroy(nlb_table *h) {
         if (hipDeviceSynchronize() != hipSuccess) rc = NLB_EDEVICE;
         if (hipFree(h->blocks) != hipSuccess) rc = NLB_EDEVICE;
         if (h->rnn_winner && hipFree(h->rnn_winner) != hipSuccess) rc = NLB_EDEVICE;
-        if (h->rnn_cand && hipFree(h->rnn_cand) != hipSuccess) rc = NLB_EDEVICE;
+        if (h->rnn_stage && hipFree(h->rnn_stage) != hipSuccess) rc = NLB_EDEVICE;
         if (h->rnn_list && hipFree(h->rnn_list) != hipSuccess) rc = NLB_EDEVICE;
     }
     delete h;

@@ -59,6 +59,10 @@ constexpr size_t kStatusBytes = 256;
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+// The same at 4-byte alignment, which global loads and stores of 16 bytes
+// allow on gfx950.
+typedef uint32_t u32x4_at4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef float f32x4_at4 __attribute__((ext_vector_type(4), aligned(4)));
 
 // ---------------------------------------------------------------- cosine
 // Arguments beyond the fast path's range: the device libm's double cos,
@@ -287,9 +291,9 @@ struct nlb_table {
     // Node-status update (rnn.hip), allocated on first use.
     unsigned long long *rnn_winner;   // [N] latest pair-row code per node, zero between calls
     int32_t rnn_form;                 // GRU pass of the last update (NLB_RNN_FORM_*)
-    uint8_t *rnn_cand;                // candidate status rows by pair row
-    size_t rnn_cand_bytes;
+    uint8_t *rnn_stage;               // the winners' r_other by list position, then the packed weights
+    size_t rnn_stage_bytes;
     uint32_t *rnn_list;               // winner count, then the winners' pair rows
-    uint64_t rnn_cand_rows;
+    uint64_t rnn_stage_rows;
 };
 

@@ -11,18 +11,20 @@
 // update of its latest one (larger arrival index; on a self-loop the second
 // endpoint's).
 //
-// Four launches per batch:
+// Three launches per batch:
 //   resolve  each endpoint offers the code 2i + k + 1 of its pair row (link
 //            i, endpoint k) to winner[node] with a 64-bit atomic maximum (the
-//            array is all zero between calls: the scatter clears the words it
-//            has used).  Large batches merge their offers per node in LDS
-//            first (merge_max), as the table insertion does.
-//   select   each pair row checks whether it won; the winners are appended
-//            to a dense list (one atomic per wavefront).  The list order
-//            varies from run to run; the results do not, because every row
-//            of a matrix product depends on its own inputs only.  The same
-//            launch repacks the weights into matrix-operand fragments, so
+//            array is all zero between calls: the gru pass clears the words
+//            it has used).  Large batches merge their offers per node in LDS
+//            first (merge_max), as the table insertion does.  Workgroups
+//            beside them repack the weights into matrix-operand fragments, so
 //            that the gru pass reads each with one contiguous 1 KB load.
+//   select   each pair row checks whether it won; the winners are appended
+//            to a dense list (one global atomic per workgroup).  The list
+//            order varies from run to run; the results do not, because every
+//            row of a matrix product depends on its own inputs only.  The
+//            same launch copies the winners' r_other into staged rows, by
+//            list position.
 //   gru      where its registers suffice, the weight-stationary form
 //            (rnn_gru_ws: one workgroup per CU keeps the weights in
 //            registers and loops over 32-row tiles of listed rows);
@@ -30,15 +32,18 @@
 //            and reads the weights from L2 (rnn_gru).  Both build the inputs
 //            in LDS and run both GRU products on bf16 matrix cores; the
 //            gates, the blend with h and the rounding to the status type
-//            happen in registers, and the new status goes to a candidate
-//            buffer indexed by pair row.
-//   scatter  copies each listed winner's candidate row over its node's
-//            status and clears the node's winner word.  Every node a valid
-//            link touches has exactly one winner, so this restores the all-
-//            zero array; no call number is needed, and a call captured in a
-//            HIP graph can be replayed.
-// The candidate buffer is what lets the gru pass read only pre-batch
-// statuses: no status is written until every workgroup has read its inputs.
+//            happen in registers, and the new status goes over the old one.
+//            The node's winner word is cleared: every node a valid link
+//            touches has exactly one winner, so this restores the all-zero
+//            array; no call number is needed, and a call captured in a HIP
+//            graph can be replayed.
+// The staged rows are what lets the gru pass write statuses while other tiles
+// are still to be read: a tile reads r_other from them, and from the statuses
+// only the rows of its own nodes, which no other tile reads or writes.  (The
+// new statuses went to candidate rows before, and a fourth launch copied them
+// over the statuses: that launch read and wrote them once more, where staging
+// moves the read of r_other from one kernel to another and adds one write and
+// one read of a row, both contiguous.)
 //
 // Numerics.  fp32 activations (fp32 statuses, the time encoding, fp32 link
 // rows) enter the products as bf16 pairs hi + lo (2^-18 relative), bf16 ones
@@ -76,13 +81,39 @@ struct ResolveParams {
     unsigned long long *winner;
     uint32_t *status;
     uint32_t *count;      // winners listed by select; zeroed here
+    uint32_t link_blocks; // workgroups that take links; the others pack the weights
+    // The GRU weights, repacked in operand-fragment order for the GRU
+    // pass: fragment (unit block b < kd / 16, k-step s < ks, gate g) is 64
+    // lanes x 16 bytes at ((b * ks + s) * 3 + g) * 64, lane l holding unit
+    // 16 b + l % 16 (clamped to d - 1), columns 32 s' + 8 (l / 16) .. + 7 of
+    // W_i (steps s < kxm = kx / 32, s' = s) or of W_h (s' = s - kxm).
+    const __bf16 *w_ih, *w_hh;
+    u32x4 *wpack;
+    uint32_t d, kx, kd, kxm, ks, pieces;
 };
+
+// The weight pack, by the workgroups past the links' (T threads each): each
+// 16-byte piece read once (row reads of 64 bytes) and written once,
+// contiguous in the order the GRU pass loads them.  It depends on nothing in
+// the batch, so it runs beside the atomics.
+template <uint32_t T>
+__device__ __forceinline__ void pack_weights(const ResolveParams &p) {
+    for (uint32_t q = (blockIdx.x - p.link_blocks) * T + threadIdx.x; q < p.pieces;
+         q += (gridDim.x - p.link_blocks) * T) {
+        const uint32_t l = q & 63u, f = q >> 6, g = f % 3u, s = (f / 3u) % p.ks, b = f / (3u * p.ks);
+        const uint32_t jr = min(16u * b + (l & 15u), p.d - 1u), lk = (l >> 4) * 8u;
+        const __bf16 *src = s < p.kxm ? p.w_ih + ((size_t)g * p.d + jr) * p.kx + 32u * s + lk
+                                      : p.w_hh + ((size_t)g * p.d + jr) * p.kd + 32u * (s - p.kxm) + lk;
+        p.wpack[q] = *(const u32x4 *)src;
+    }
+}
 
 __device__ __forceinline__ bool endpoints_ok(int32_t u, int32_t v, int64_t num_nodes) {
     return u >= 0 && v >= 0 && (int64_t)u < num_nodes && (int64_t)v < num_nodes;
 }
 
 __global__ __launch_bounds__(kRnnThreads) void rnn_resolve(ResolveParams p) {
+    if (blockIdx.x >= p.link_blocks) return pack_weights<kRnnThreads>(p);
     const uint32_t i = blockIdx.x * kRnnThreads + threadIdx.x;
     if (i == 0) *p.count = 0;
     if (i >= p.n) return;
@@ -96,6 +127,7 @@ __global__ __launch_bounds__(kRnnThreads) void rnn_resolve(ResolveParams p) {
 }
 
 __global__ __launch_bounds__(kMergeThreads) void rnn_resolve_merged(ResolveParams p) {
+    if (blockIdx.x >= p.link_blocks) return pack_weights<kMergeThreads>(p);
     __shared__ unsigned long long merge_off[kMergeEntries];
     __shared__ unsigned long long merge_word[kMergeEntries];
     for (int k = threadIdx.x; k < kMergeEntries; k += kMergeThreads) {
@@ -142,23 +174,56 @@ struct SelectParams {
     const unsigned long long *winner;
     u32x4 *list;          // winners, dense: {pair row, self, other, 0}
     uint32_t *count;
-    // The GRU weights, repacked here in operand-fragment order for the GRU
-    // pass: fragment (unit block b < kd / 16, k-step s < ks, gate g) is 64
-    // lanes x 16 bytes at ((b * ks + s) * 3 + g) * 64, lane l holding unit
-    // 16 b + l % 16 (clamped to d - 1), columns 32 s' + 8 (l / 16) .. + 7 of
-    // W_i (steps s < kxm = kx / 32, s' = s) or of W_h (s' = s - kxm).
-    const __bf16 *w_ih, *w_hh;
-    u32x4 *wpack;
-    uint32_t d, kx, kd, kxm, ks, pieces;
+    // The statuses r_other of the winners, staged by list position, so that
+    // the GRU pass may overwrite statuses while other tiles are still to be
+    // read (a winner's own status is read by its own tile only).
+    const uint8_t *st;
+    uint8_t *stage;
+    uint32_t srb, w, upr;  // bytes per row, copy unit (bytes), units per row
+    uint64_t upr_m;        // nlb_div_magic(upr)
 };
 
-// A workgroup checks kSelectRows consecutive pair rows, collects its
-// winners in LDS (one LDS atomic per wavefront and pass) and appends them to
-// the list with a single global atomic.
-constexpr uint32_t kSelectRows = 1024;
+// The staged rows of a workgroup's winners (n of them, in `rows`), copied in
+// units of V (the last unit of a row from the row's end backwards, so that any
+// row of at least one unit copies in whole units: two threads may write a byte
+// twice, with the same value) from position `at()` of the list on; at() is
+// called once, by every thread, after the first R units of each thread have
+// been requested.
+template <uint32_t T, typename V, int R, typename At>
+__device__ __forceinline__ void stage_rows(const SelectParams &p, const u32x4 *rows, uint32_t n, At at) {
+    const uint32_t total = n * p.upr, last = p.srb - (uint32_t)sizeof(V);
+    V v[R];
+    uint32_t off[R];   // where in the staged rows
+    auto request = [&](uint32_t base) {
+#pragma unroll
+        for (int q = 0; q < R; q++) {
+            const uint32_t u = min(base + q * T, total - 1u), k = nlb_div(u, p.upr_m);
+            const uint32_t o = min((u - k * p.upr) * (uint32_t)sizeof(V), last);
+            off[q] = k * p.srb + o;
+            v[q] = *(const V *)(p.st + (size_t)rows[k][2] * p.srb + o);
+        }
+    };
+    if (total) request(threadIdx.x);
+    uint8_t *to = p.stage + at() * p.srb;
+    for (uint32_t base = threadIdx.x; base < total; base += T * R) {
+        if (base >= T * R) request(base);
+#pragma unroll
+        for (int q = 0; q < R; q++)
+            if (base + q * T < total) *(V *)(to + off[q]) = v[q];
+    }
+}
 
-__global__ __launch_bounds__(kRnnThreads) void rnn_select(SelectParams p) {
-    __shared__ u32x4 rows[kSelectRows];
+constexpr uint64_t kSelectSmall = 128 * 256;   // pair rows up to which select's workgroups have 256 threads
+
+// A workgroup checks T consecutive pair rows, one per thread, collects its
+// winners in LDS (one LDS atomic per wavefront) and appends them to the list
+// with a single global atomic.  All workgroups' atomics go to one word, which
+// takes them about 12 ns apart: 200 000 pair rows in workgroups of 256 threads
+// (782 atomics) took 16.0 us, of 512 13.0 and of 1024 11.3, so large batches use
+// 1024; small ones use 256, which spreads their rows over more CUs.
+template <uint32_t T>
+__global__ __launch_bounds__(T) void rnn_select(SelectParams p) {
+    __shared__ u32x4 rows[T];
     __shared__ uint32_t n_local, base;
     const uint32_t lane = threadIdx.x & 63;
     if (threadIdx.x == 0) n_local = 0;
@@ -167,25 +232,25 @@ __global__ __launch_bounds__(kRnnThreads) void rnn_select(SelectParams p) {
     // of their nodes, are read in two rounds of unconditional loads (rows
     // past the batch re-read the last link; invalid endpoints read
     // winner[0]) before any is used.
-    constexpr int RS = kSelectRows / kRnnThreads;
-    const uint64_t r0 = (uint64_t)blockIdx.x * kSelectRows;
+    constexpr int RS = T / T;
+    const uint64_t r0 = (uint64_t)blockIdx.x * T;
     int32_t su[RS], sv[RS];
 #pragma unroll
     for (int q = 0; q < RS; q++) {
-        const uint64_t r = min(r0 + q * kRnnThreads + threadIdx.x, 2ull * p.n - 1ull);
+        const uint64_t r = min(r0 + q * T + threadIdx.x, 2ull * p.n - 1ull);
         su[q] = p.src[(uint32_t)(r >> 1)];
         sv[q] = p.dst[(uint32_t)(r >> 1)];
     }
     unsigned long long wv[RS];
 #pragma unroll
     for (int q = 0; q < RS; q++) {
-        const uint64_t r = min(r0 + q * kRnnThreads + threadIdx.x, 2ull * p.n - 1ull);
+        const uint64_t r = min(r0 + q * T + threadIdx.x, 2ull * p.n - 1ull);
         const int32_t self = (r & 1) ? sv[q] : su[q];
         wv[q] = p.winner[endpoints_ok(su[q], sv[q], p.num_nodes) ? self : 0];
     }
 #pragma unroll
     for (int q = 0; q < RS; q++) {
-        const uint32_t k = q * kRnnThreads + threadIdx.x;
+        const uint32_t k = q * T + threadIdx.x;
         const uint64_t r = r0 + k;
         bool win = false;
         int32_t self = -1, other = -1;
@@ -208,20 +273,21 @@ __global__ __launch_bounds__(kRnnThreads) void rnn_select(SelectParams p) {
                 u32x4{(uint32_t)r, (uint32_t)self, (uint32_t)other, 0u};
     }
     __syncthreads();
-    if (threadIdx.x == 0) base = n_local ? atomicAdd(p.count, n_local) : 0;
-    __syncthreads();
-    for (uint32_t k = threadIdx.x; k < n_local; k += kRnnThreads) p.list[base + k] = rows[k];
-    // The weight pack: each 16-byte piece read once (row reads of 64 bytes)
-    // and written once, contiguous in the order the GRU pass loads them.
-    if (p.wpack) {
-        for (uint32_t q = blockIdx.x * kRnnThreads + threadIdx.x; q < p.pieces; q += gridDim.x * kRnnThreads) {
-            const uint32_t l = q & 63u, f = q >> 6, g = f % 3u, s = (f / 3u) % p.ks, b = f / (3u * p.ks);
-            const uint32_t jr = min(16u * b + (l & 15u), p.d - 1u), lk = (l >> 4) * 8u;
-            const __bf16 *src = s < p.kxm ? p.w_ih + ((size_t)g * p.d + jr) * p.kx + 32u * s + lk
-                                          : p.w_hh + ((size_t)g * p.d + jr) * p.kd + 32u * (s - p.kxm) + lk;
-            p.wpack[q] = *(const u32x4 *)src;
-        }
-    }
+    // The workgroup's place in the list and the list entries, while the first
+    // of its rows are on their way.
+    const uint32_t n = n_local;
+    auto at = [&]() -> uint64_t {
+        if (threadIdx.x == 0) base = n ? atomicAdd(p.count, n) : 0;
+        __syncthreads();
+        for (uint32_t k = threadIdx.x; k < n; k += T) p.list[base + k] = rows[k];
+        return base;
+    };
+    if (p.w == 16)
+        stage_rows<T, u32x4_at4, 8>(p, rows, n, at);
+    else if (p.w == 4)
+        stage_rows<T, uint32_t, 8>(p, rows, n, at);
+    else
+        stage_rows<T, uint16_t, 8>(p, rows, n, at);
 }
 
 struct GruParams {
@@ -240,9 +306,10 @@ struct GruParams {
     const uint8_t *efeat;
     int64_t edge_rows;
     uint32_t e_dim, e_bf16, erb, e_vec;
-    const uint8_t *st;                  // statuses [N][d]
-    uint32_t s_bf16, srb, s_vec;
-    uint8_t *cand;                      // [2n][srb] candidate rows by pair row
+    uint8_t *st;                        // statuses [N][d]
+    uint32_t s_bf16, srb, s_vec, o_vec; // (s_vec, o_vec: status / staged rows 16-byte aligned)
+    const uint8_t *stage;               // [winners][srb] the winners' r_other, by list position
+    unsigned long long *winner;         // cleared for every listed node
     uint32_t kd, off_e, kx;             // X = [r_other | T-enc | e]: columns [0,kd) [kd,off_e) [off_e,kx)
     uint32_t lo_begin, lo_end;          // X columns with a stored lo plane
     uint32_t h_lo;                      // fp32 statuses: H has a lo plane
@@ -402,11 +469,12 @@ __device__ __forceinline__ void fill_seg(uint32_t units, uint32_t g, uint64_t g_
 // j < m (rows m .. 16 NB - 1 are written as zeros), as bf16 hi planes at Xh
 // and Hh and lo planes at Xl (columns [lo_begin, lo_end)) and Hl (fp32
 // statuses), with row strides xs, ls, hs -- in LDS or in global memory.
-// m_row .. m_t are the tile rows' list entries and link times, s_tw / s_tb
+// m_row .. m_t are the tile rows' list entries and link times, others their
+// staged rows r_other, s_tw / s_tb
 // the zero-padded time-encoding parameters (LDS).  The caller synchronises.
 template <int NB>
 __device__ __forceinline__ void gru_fill(const GruParams &p, uint32_t m, const uint32_t *m_row,
-                                         const int32_t *m_self, const int32_t *m_other, const float *m_t,
+                                         const int32_t *m_self, const uint8_t *others, const float *m_t,
                                          const float *s_tw, const float *s_tb, __bf16 *Xh, __bf16 *Xl,
                                          __bf16 *Hh, __bf16 *Hl, uint32_t xs, uint32_t ls, uint32_t hs) {
     const uint64_t first_eid = first_eid_of(p);
@@ -428,9 +496,8 @@ __device__ __forceinline__ void gru_fill(const GruParams &p, uint32_t m, const u
             fill_seg<K, 8>(
                 2u * us, gh, p.gh_m, d,
                 [&](uint32_t jj) {
-                    const uint32_t j = jj < R ? jj : jj - R;
-                    const int32_t node = (jj < R ? m_self : m_other)[j < m ? j : 0];
-                    return p.st + (size_t)node * p.srb;
+                    const uint32_t j = jj < R ? jj : jj - R, jm = j < m ? j : 0;
+                    return jj < R ? (const uint8_t *)p.st + (size_t)m_self[jm] * p.srb : others + (size_t)jm * p.srb;
                 },
                 [&](uint32_t jj, uint32_t c0, const Piece8<K> &pc) {
                     const uint32_t j = jj < R ? jj : jj - R;
@@ -533,7 +600,7 @@ __device__ __forceinline__ void gru_fill(const GruParams &p, uint32_t m, const u
             if (j >= m) continue;
             const uint32_t link = m_row[j] >> 1;
             if (c0 < p.kd) {
-                load8(p.st + (size_t)m_other[j] * p.srb, p.d, p.s_bf16, p.s_vec, c0, v[f]);
+                load8(others + (size_t)j * p.srb, p.d, p.s_bf16, p.o_vec, c0, v[f]);
             } else if (c0 < p.off_e) {
                 const uint32_t k = c0 - p.kd;
                 const float tf = (float)p.t[link];
@@ -595,8 +662,7 @@ __global__ __launch_bounds__(kRnnThreads) void rnn_gru(GruParams p) {
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
     uint32_t *m_row = (uint32_t *)smem;          // pair row of tile row j
     int32_t *m_self = (int32_t *)(m_row + 64);
-    int32_t *m_other = m_self + 64;
-    float *m_t = (float *)(m_other + 64);        // its link's time, as fp32
+    float *m_t = (float *)(m_self + 64);         // its link's time, as fp32
     float *s_tw = (float *)(smem + kGruMetaRows), *s_tb = s_tw + ((p.d_time + 31u) & ~31u);
     __bf16 *Xh = (__bf16 *)(smem + p.meta);
     __bf16 *Xl = (__bf16 *)(smem + p.off_xl);
@@ -613,7 +679,7 @@ __global__ __launch_bounds__(kRnnThreads) void rnn_gru(GruParams p) {
         const u32x4 e = p.list[j0 + tid];
         m_row[tid] = e[0];
         m_self[tid] = (int32_t)e[1];
-        m_other[tid] = (int32_t)e[2];
+        p.winner[e[1]] = 0ull;
         m_t[tid] = (float)p.t[e[0] >> 1];
     }
     for (uint32_t u = tid; u < ((p.d_time + 31u) & ~31u); u += kRnnThreads) {
@@ -622,7 +688,7 @@ __global__ __launch_bounds__(kRnnThreads) void rnn_gru(GruParams p) {
     }
     __syncthreads();
 
-    gru_fill<NB>(p, m, m_row, m_self, m_other, m_t, s_tw, s_tb, Xh, Xl, Hh, Hl, p.xs, p.ls, p.hs);
+    gru_fill<NB>(p, m, m_row, m_self, p.stage + j0 * p.srb, m_t, s_tw, s_tb, Xh, Xl, Hh, Hl, p.xs, p.ls, p.hs);
     __syncthreads();
 
     const uint32_t d = p.d;
@@ -672,11 +738,11 @@ __global__ __launch_bounds__(kRnnThreads) void rnn_gru(GruParams p) {
                 const float zg = sigmoid_f32(acc[1][rb][i] + bz);
                 const float ng = tanh_f32(acc[2][rb][i] + bin + rg * (acc[3][rb][i] + bhn));
                 const float out = (1.0f - zg) * ng + zg * hv[rb][i];
-                uint8_t *crow = p.cand + (size_t)m_row[row] * p.srb;
+                uint8_t *srow = p.st + (size_t)m_self[row] * p.srb;
                 if (p.s_bf16)
-                    ((uint16_t *)crow)[j] = f32_to_bf16_rne(out);
+                    ((uint16_t *)srow)[j] = f32_to_bf16_rne(out);
                 else
-                    ((float *)crow)[j] = out;
+                    ((float *)srow)[j] = out;
             }
         }
     }
@@ -708,7 +774,7 @@ __global__ __launch_bounds__(kRnnThreads) void rnn_gru(GruParams p) {
 // output units of one tile row: the accumulators start from the gate
 // biases, the gates read the units' h values with one 8-byte LDS read (a
 // 16-byte global read for fp32 statuses), and the new statuses go straight
-// from registers to the candidate rows, 8 or 16 bytes per lane, with no
+// from registers to the status rows, 8 or 16 bytes per lane, with no
 // exchange between wavefronts.
 //
 // The two wavefronts that share a SIMD (w and w + KH) alternate between
@@ -777,7 +843,7 @@ __device__ __forceinline__ void lds_load4(const void *g, uint32_t lds) {
 
 __device__ __forceinline__ uint32_t lds_addr(const void *p) { return (uint32_t)(uintptr_t)(lds_ptr)p; }
 
-// Candidate-row stores, written as assembly: the compiler would otherwise
+// Status stores, written as assembly: the compiler would otherwise
 // make the next write of their source registers wait until the stores have
 // completed (vmcnt), which stalls the loop for a memory round trip; the
 // hardware has read the sources one wait state after issue (the nop).
@@ -790,7 +856,7 @@ __device__ __forceinline__ void store_b128_async(void *g, u32x4 v) {
 
 // Workgroup barriers of the tile loop.  The first half has no direct loads
 // in flight and nothing in global memory that another wavefront reads, so it
-// waits for its LDS accesses only (its candidate-row stores complete in the
+// waits for its LDS accesses only (its status stores complete in the
 // background); the second half also waits for its direct loads (vmcnt), which
 // the compiler does not count.
 __device__ __forceinline__ void barrier_lds() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
@@ -859,18 +925,16 @@ __global__ __launch_bounds__(128 * KH) void rnn_gru_ws(GruParams p) {
     // l % 16, columns 32 (f / NB) + 8 (l / 16) .. + 7.  Register path: a
     // thread's status pieces, f = 0 of H (self) and f = 1 of X's r_other,
     // both at tile row pj, columns pc0 .. pc0 + 7, written to LDS later.
-    auto request_frag = [&](uint8_t *nbS, uint32_t slot, uint32_t f) __attribute__((always_inline)) {
+    auto request_frag = [&](uint8_t *nbS, uint32_t slot, uint32_t tl, uint32_t f) __attribute__((always_inline)) {
         const uint32_t dj = 16 * (f % NB) + lr, dc = 32 * (f / NB) + lk;
-        const u32x4 e = meta[slot * MS + dj];
-        lds_load16(p.st + (size_t)e[1] * p.srb + 2u * dc, lds_addr(nbS + L::sh + f * FB));
-        lds_load16(p.st + (size_t)e[2] * p.srb + 2u * dc, lds_addr(nbS + L::sx + f * FB));
+        lds_load16(p.st + (size_t)meta[slot * MS + dj][1] * p.srb + 2u * dc, lds_addr(nbS + L::sh + f * FB));
+        lds_load16(p.stage + list_at(tl, dj) * p.srb + 2u * dc, lds_addr(nbS + L::sx + f * FB));
     };
     const uint32_t pj = tid / GH, pc0 = 8 * (tid % GH);
     Piece8<SK> pc[2];
-    auto request_pieces = [&](uint32_t slot) __attribute__((always_inline)) {
-        const u32x4 e = meta[slot * MS + pj];
-        load_piece<SK>(p.st + (size_t)e[1] * p.srb, d, pc0, pc[0]);
-        load_piece<SK>(p.st + (size_t)e[2] * p.srb, d, pc0, pc[1]);
+    auto request_pieces = [&](uint32_t slot, uint32_t tl) __attribute__((always_inline)) {
+        load_piece<SK>(p.st + (size_t)meta[slot * MS + pj][1] * p.srb, d, pc0, pc[0]);
+        load_piece<SK>(p.stage + list_at(tl, pj) * p.srb, d, pc0, pc[1]);
     };
     auto write_pieces = [&](uint8_t *nbS, uint8_t *nbT) __attribute__((always_inline)) {
         const uint32_t po = frag_off(pj, pc0);
@@ -1061,9 +1125,9 @@ __global__ __launch_bounds__(128 * KH) void rnn_gru_ws(GruParams p) {
             for (int g = 0; g < 3; g++) bh[s][g] = __builtin_bit_cast(bf16x8, wf[((kx_steps + s) * 3u + g) * 64u]);
     }
     if constexpr (MODE == kWsBf16Dma)
-        request_frag(bs0, 0, wave);
+        request_frag(bs0, 0, tl, wave);
     else
-        request_pieces(0);
+        request_pieces(0, tl);
     __builtin_amdgcn_sched_barrier(0);
     // Wait for the two link-time loads only: at least the 36 weight loads
     // were issued after them, and loads complete in order.
@@ -1154,7 +1218,7 @@ __global__ __launch_bounds__(128 * KH) void rnn_gru_ws(GruParams p) {
     // tile's H plane (bf16 statuses, packed pairs) or the status rows (fp32).
     using HvT = std::conditional_t<MODE == kWsF32, f32x4, u32x2>;
     HvT hv[NB];
-    uint32_t prow[NB];   // second half: pair rows of the tile whose gates are pending
+    uint32_t pnode[NB];  // second half: nodes of the tile whose gates are pending
     auto read_hv = [&](const uint8_t *cbS, uint32_t ms) __attribute__((always_inline)) {
 #pragma unroll
         for (int rb = 0; rb < NB; rb++) {
@@ -1172,13 +1236,14 @@ __global__ __launch_bounds__(128 * KH) void rnn_gru_ws(GruParams p) {
             return __uint_as_float(q & 1 ? hv[rb][q >> 1] & 0xFFFF0000u : hv[rb][q >> 1] << 16);
     };
     // The gates of tile tlg of the launch from acc and hv; new statuses of
-    // its listed rows to their candidate rows (pair rows pr of the lane's
-    // tile rows 16 rb + lr, read from the tile's row-list slot).
-    auto pair_rows = [&](uint32_t ms, uint32_t (&pr)[NB]) __attribute__((always_inline)) {
+    // its listed rows over their old ones (nodes nd of the lane's tile rows
+    // 16 rb + lr, read from the tile's row-list slot), and those nodes' winner
+    // words back to zero.
+    auto tile_nodes = [&](uint32_t ms, uint32_t (&nd)[NB]) __attribute__((always_inline)) {
 #pragma unroll
-        for (int rb = 0; rb < NB; rb++) pr[rb] = meta[ms * MS + 16u * rb + lr][0];
+        for (int rb = 0; rb < NB; rb++) nd[rb] = meta[ms * MS + 16u * rb + lr][1];
     };
-    auto gates = [&](const uint32_t (&pr)[NB], uint32_t tlg) __attribute__((always_inline)) {
+    auto gates = [&](const uint32_t (&nd)[NB], uint32_t tlg) __attribute__((always_inline)) {
         const uint32_t nrows = min(R, count - tlg * R);
 #pragma unroll
         for (int rb = 0; rb < NB; rb++) {
@@ -1192,7 +1257,8 @@ __global__ __launch_bounds__(128 * KH) void rnn_gru_ws(GruParams p) {
                 out[q] = __builtin_fmaf(zg, h_at(rb, q) - ng, ng);   // (1 - z) n + z h
             }
             if (u0 < d && row < nrows) {
-                uint8_t *dst = p.cand + (size_t)pr[rb] * p.srb;
+                uint8_t *dst = p.st + (size_t)nd[rb] * p.srb;
+                if (u0 == 0) store_b64_async(p.winner + nd[rb], u32x2{0u, 0u});
                 if constexpr (MODE == kWsF32) {
                     store_b128_async(dst + 4u * u0, u32x4{__float_as_uint(out[0]), __float_as_uint(out[1]),
                                                           __float_as_uint(out[2]), __float_as_uint(out[3])});
@@ -1213,18 +1279,18 @@ __global__ __launch_bounds__(128 * KH) void rnn_gru_ws(GruParams p) {
     // tile's time encoding (units tid, tid + T, ..., as in the second half)
     // and the link rows; false after the workgroup's last tile.  (No loads here
     // on the direct path: a wait for one would also wait for the last tile's
-    // candidate-row stores.)
+    // status stores.)
     auto tile_first = [&](uint8_t *cbS, uint8_t *cbT, uint8_t *nbS, uint8_t *nbT, uint32_t i)
                           __attribute__((always_inline)) {
         const uint32_t ms = i & 7;
         const bool has_next = tl + stride < tiles;
-        if (MODE != kWsBf16Dma && has_next) request_pieces((i + 1) & 7);
+        if (MODE != kWsBf16Dma && has_next) request_pieces((i + 1) & 7, tl + stride);
         if (mma) {
             products(cbS, cbT);
             read_hv(cbS, ms);
-            uint32_t pr[NB];
-            pair_rows(ms, pr);
-            gates(pr, tl);
+            uint32_t nd[NB];
+            tile_nodes(ms, nd);
+            gates(nd, tl);
         }
         if (has_next) {
             for (uint32_t u = tid; u < tu; u += T) tenc_unit(nbT, u, (float)tt[(i + 1) & 3][unit_row(u)]);
@@ -1252,13 +1318,13 @@ __global__ __launch_bounds__(128 * KH) void rnn_gru_ws(GruParams p) {
             lds_load4(p.t + (meta[((i + 2) & 7) * MS + (lane & (R - 1))][0] >> 1), lds_addr(tt[(i + 2) & 3]));
         if (has_next) {
             if constexpr (MODE == kWsBf16Dma) {
-                request_frag(nbS, ns, wave - KH);
-                request_frag(nbS, ns, wave);
+                request_frag(nbS, ns, tl + stride, wave - KH);
+                request_frag(nbS, ns, tl + stride, wave);
             } else {
-                request_pieces(ns);
+                request_pieces(ns, tl + stride);
             }
         }
-        if (i > 0 && mma) gates(prow, tl - stride);
+        if (i > 0 && mma) gates(pnode, tl - stride);
         if (has_next) {
             for (uint32_t u = tid; u < tu; u += T) tenc_unit(nbT, u, (float)tt[(i + 1) & 3][unit_row(u)]);
             if (MODE != kWsBf16Dma) write_pieces(nbS, nbT);
@@ -1266,7 +1332,7 @@ __global__ __launch_bounds__(128 * KH) void rnn_gru_ws(GruParams p) {
         if (mma) {
             products(cbS, cbT);
             read_hv(cbS, ms);
-            pair_rows(ms, prow);
+            tile_nodes(ms, pnode);
         }
         barrier_loads();
         tl += stride;
@@ -1286,43 +1352,7 @@ __global__ __launch_bounds__(128 * KH) void rnn_gru_ws(GruParams p) {
                 break;
             }
         }
-        if (mma) gates(prow, tl - stride);   // the workgroup's last tile
-    }
-}
-
-// Status rows of the winners: for each listed winner {pair row r, node},
-// candidate row r -> status row node, in units of `w` bytes (upr units per
-// row), and winner[node] = 0.  A wavefront pass copies 64 >> lg rows
-// (lg = ceil(log2 upr) <= 6), or one row in passes of 64 units; wavefronts
-// stride over the list.
-__global__ __launch_bounds__(kRnnThreads) void rnn_scatter(const uint8_t *cand, const u32x4 *list,
-                                                          const uint32_t *count, uint8_t *st, uint32_t srb,
-                                                          uint32_t w, uint32_t upr, uint32_t lg,
-                                                          unsigned long long *winner) {
-    const uint32_t n = *count, lane = threadIdx.x & 63;
-    const uint64_t gw = ((uint64_t)blockIdx.x * kRnnThreads + threadIdx.x) >> 6;
-    const uint64_t nw = ((uint64_t)gridDim.x * kRnnThreads) >> 6;
-    auto copy = [&](uint64_t k, uint32_t c) {
-        const u32x4 e = list[k];
-        const uint8_t *from = cand + (size_t)e[0] * srb + c * w;
-        uint8_t *to = st + (size_t)e[1] * srb + c * w;
-        if (w == 16)
-            *(u32x4 *)to = *(const u32x4 *)from;
-        else if (w == 8)
-            *(u32x2 *)to = *(const u32x2 *)from;
-        else if (w == 4)
-            *(uint32_t *)to = *(const uint32_t *)from;
-        else
-            *(uint16_t *)to = *(const uint16_t *)from;
-        if (c == 0) winner[e[1]] = 0ull;
-    };
-    if (lg <= 6) {
-        const uint32_t per = 64u >> lg, c = lane & ((1u << lg) - 1u);
-        for (uint64_t k = gw * per + (lane >> lg); k < n; k += nw * per)
-            if (c < upr) copy(k, c);
-    } else {
-        for (uint64_t k = gw; k < n; k += nw)
-            for (uint32_t c = lane; c < upr; c += 64) copy(k, c);
+        if (mma) gates(pnode, tl - stride);   // the workgroup's last tile
     }
 }
 
@@ -1345,7 +1375,7 @@ uint32_t gru_layout(GruParams &p, uint32_t rows) {
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // Per-table working memory of the update, grown on demand: the winner
-// words, the list, and one buffer for the candidate rows followed (at a
+// words, the list, and one buffer for the staged rows followed (at a
 // 256-byte boundary) by the packed GRU weights.
 int rnn_reserve(nlb_table *h, uint64_t pair_rows, uint32_t srb, size_t wpack_bytes) {
     if (!h->rnn_winner) {
@@ -1358,36 +1388,36 @@ int rnn_reserve(nlb_table *h, uint64_t pair_rows, uint32_t srb, size_t wpack_byt
         if (hipMemset(h->rnn_winner, 0, bytes) != hipSuccess) return NLB_EDEVICE;
     }
     const size_t cbytes = align256((size_t)pair_rows * srb) + wpack_bytes;
-    if (cbytes > h->rnn_cand_bytes || pair_rows > h->rnn_cand_rows) {
+    if (cbytes > h->rnn_stage_bytes || pair_rows > h->rnn_stage_rows) {
         // Earlier updates may still read the old buffers.
         if (hipDeviceSynchronize() != hipSuccess) return NLB_EDEVICE;
-        (void)hipFree(h->rnn_cand);
+        (void)hipFree(h->rnn_stage);
         (void)hipFree(h->rnn_list);
-        h->rnn_cand = nullptr;
+        h->rnn_stage = nullptr;
         h->rnn_list = nullptr;
-        h->rnn_cand_bytes = 0;
-        h->rnn_cand_rows = 0;
+        h->rnn_stage_bytes = 0;
+        h->rnn_stage_rows = 0;
         // list: the winner count in word 0, the winners (4 words each) from word 64 on
-        if (hipMalloc((void **)&h->rnn_cand, cbytes) != hipSuccess ||
+        if (hipMalloc((void **)&h->rnn_stage, cbytes) != hipSuccess ||
             hipMalloc((void **)&h->rnn_list, ((size_t)pair_rows * 4u + 64u) * 4u) != hipSuccess) {
             (void)hipGetLastError();
-            (void)hipFree(h->rnn_cand);
-            h->rnn_cand = nullptr;
+            (void)hipFree(h->rnn_stage);
+            h->rnn_stage = nullptr;
             h->rnn_list = nullptr;
             return NLB_ENOMEM;
         }
-        h->rnn_cand_bytes = cbytes;
-        h->rnn_cand_rows = pair_rows;
+        h->rnn_stage_bytes = cbytes;
+        h->rnn_stage_rows = pair_rows;
     }
     return NLB_OK;
 }
 
 // Working memory of one update: the winner word of every node (all zero
-// between calls), the winner count and list, and the candidate rows.
+// between calls), the winner count and list, and the staged rows.
 struct RnnWork {
     unsigned long long *winner;
     bool clear_winner;    // zero winner[0 .. N) first (memory shared with other calls)
-    uint8_t *cand;
+    uint8_t *stage;
     uint32_t *list;       // word 0: winner count; from word 64: the winners, 4 words each
     uint8_t *wpack;       // the weights in operand-fragment order
 };
@@ -1396,8 +1426,8 @@ struct RnnWork {
 int table_work(nlb_table *h, uint64_t pairs, uint32_t srb, size_t wpack_bytes, RnnWork *wk) {
     const int rc = rnn_reserve(h, pairs, srb, wpack_bytes);
     if (rc != NLB_OK) return rc;
-    *wk = {h->rnn_winner, false, h->rnn_cand, h->rnn_list,
-           wpack_bytes ? h->rnn_cand + align256((size_t)pairs * srb) : nullptr};
+    *wk = {h->rnn_winner, false, h->rnn_stage, h->rnn_list,
+           wpack_bytes ? h->rnn_stage + align256((size_t)pairs * srb) : nullptr};
     return NLB_OK;
 }
 
@@ -1433,14 +1463,14 @@ int scratch_address(int dev, uint8_t **out) {
 }
 
 // The update's working memory carved from `scratch`: winner words of all N
-// nodes, the list, the packed weights, the candidate rows.  The winner words are cleared by a fill kernel at the
-// start of every call.
+// nodes, the list, the packed weights, the staged rows.  The winner words are
+// cleared by a fill kernel at the start of every call.
 int scratch_work(nlb_table *h, uint64_t pairs, uint32_t srb, size_t wpack_bytes, RnnWork *wk) {
     const size_t winner_bytes = align256((size_t)h->num_nodes * 8u);
     const size_t list_bytes = align256(((size_t)pairs * 4u + 64u) * 4u);
     const size_t pack_bytes = align256(wpack_bytes);
-    const size_t cand_bytes = (size_t)pairs * srb;
-    if (winner_bytes + list_bytes + pack_bytes + cand_bytes > kScratchBytes) return NLB_ESCRATCH;
+    const size_t stage_bytes = (size_t)pairs * srb;
+    if (winner_bytes + list_bytes + pack_bytes + stage_bytes > kScratchBytes) return NLB_ESCRATCH;
     uint8_t *base = nullptr;
     const int rc = scratch_address(h->device, &base);
     if (rc != NLB_OK) return rc;
@@ -1493,7 +1523,7 @@ static int rnn_update(nlb_table *h, const int32_t *src, const int32_t *dst, cons
     p.e_bf16 = ed == NLB_DTYPE_BF16;
     p.erb = h->erb;
     p.e_vec = h->erb % 16 == 0 && (uintptr_t)h->efeat % 16 == 0;
-    p.st = (const uint8_t *)status;
+    p.st = (uint8_t *)status;
     p.s_bf16 = sd == NLB_DTYPE_BF16;
     p.srb = p.d * s_es;
     p.s_vec = p.srb % 16 == 0 && (uintptr_t)status % 16 == 0;
@@ -1574,23 +1604,38 @@ static int rnn_update(nlb_table *h, const int32_t *src, const int32_t *dst, cons
     u32x4 *list = (u32x4 *)(wk.list + 64);
     p.list = list;
     p.count = count;
-    p.cand = wk.cand;
+    p.stage = wk.stage;
+    p.winner = wk.winner;
+    p.o_vec = p.srb % 16 == 0;
 
-    ResolveParams rp = {src, dst, n, h->num_nodes, wk.winner, h->status, count};
-    if (n >= kMergeMinBatch)
-        hipLaunchKernelGGL(rnn_resolve_merged, dim3((n + kResolveLinks - 1) / kResolveLinks),
+    ResolveParams rp = {src, dst, n, h->num_nodes, wk.winner, h->status, count, 0,
+                        p.w_ih, p.w_hh, (u32x4 *)wk.wpack, p.d, p.kx, p.kd, p.kx / 32, (p.kx + p.kd) / 32,
+                        (uint32_t)(wpack_bytes / 16)};
+    // (the weight pack by workgroups of its own: one piece per thread)
+    if (n >= kMergeMinBatch) {
+        rp.link_blocks = (n + kResolveLinks - 1) / kResolveLinks;
+        hipLaunchKernelGGL(rnn_resolve_merged, dim3(rp.link_blocks + (rp.pieces + kMergeThreads - 1) / kMergeThreads),
                            dim3(kMergeThreads), 0, (hipStream_t)stream, rp);
+    } else {
+        rp.link_blocks = (n + kRnnThreads - 1) / kRnnThreads;
+        hipLaunchKernelGGL(rnn_resolve, dim3(rp.link_blocks + (rp.pieces + kRnnThreads - 1) / kRnnThreads),
+                           dim3(kRnnThreads), 0, (hipStream_t)stream, rp);
+    }
+    // Copy unit of the staged rows: 16 bytes at 4-byte alignment (rows of 252
+    // bytes in 4-byte units: the whole update of 556 links 27.9 us, against
+    // 23.3), else what the alignment allows.  (The staged rows start 256-byte
+    // aligned.)
+    const bool a4 = p.srb % 4 == 0 && (uintptr_t)status % 4 == 0;
+    SelectParams sp = {src, dst, n, h->num_nodes, wk.winner, list, count, p.st, wk.stage, p.srb,
+                       a4 ? (p.srb >= 16 ? 16u : 4u) : 2u, 0, 0};
+    sp.upr = (p.srb + sp.w - 1) / sp.w;
+    sp.upr_m = nlb_div_magic(sp.upr);
+    if (pairs > kSelectSmall)
+        hipLaunchKernelGGL(rnn_select<1024>, dim3((unsigned)((pairs + 1023) / 1024)), dim3(1024), 0,
+                           (hipStream_t)stream, sp);
     else
-        hipLaunchKernelGGL(rnn_resolve, dim3((n + kRnnThreads - 1) / kRnnThreads), dim3(kRnnThreads), 0,
-                           (hipStream_t)stream, rp);
-    SelectParams sp = {src, dst, n, h->num_nodes, wk.winner, list, count,
-                       p.w_ih, p.w_hh, (u32x4 *)wk.wpack, p.d, p.kx, p.kd, p.kx / 32, (p.kx + p.kd) / 32,
-                       (uint32_t)(wpack_bytes / 16)};
-    // (at least enough workgroups for the weight pack at 8 pieces per thread:
-    // workgroups past the pair rows select nothing)
-    const uint64_t sel_blocks = std::max<uint64_t>((pairs + kSelectRows - 1) / kSelectRows,
-                                                   (sp.pieces + 8u * kRnnThreads - 1) / (8u * kRnnThreads));
-    hipLaunchKernelGGL(rnn_select, dim3((unsigned)sel_blocks), dim3(kRnnThreads), 0, (hipStream_t)stream, sp);
+        hipLaunchKernelGGL(rnn_select<256>, dim3((unsigned)((pairs + 255) / 256)), dim3(256), 0, (hipStream_t)stream,
+                           sp);
     if (ws) {
         const void *kern = nullptr;
         const bool full = ws_mode == kWsBf16Dma && kh == 4 && p.kx == 32u * (kWsSteps - 4) &&
@@ -1625,21 +1670,6 @@ static int rnn_update(nlb_table *h, const int32_t *src, const int32_t *dst, cons
             hipLaunchKernelGGL(rnn_gru<1>, grid, dim3(kRnnThreads), lds, (hipStream_t)stream, p);
     }
     h->rnn_form = ws ? NLB_RNN_FORM_WEIGHT_STATIONARY : NLB_RNN_FORM_TILED;
-    uint32_t w = 2;
-    for (uint32_t c = 16; c >= 4; c /= 2)
-        if (p.srb % c == 0 && (uintptr_t)status % c == 0 && (uintptr_t)wk.cand % c == 0) {
-            w = c;
-            break;
-        }
-    const uint32_t upr = p.srb / w;
-    uint32_t lg = 0;
-    while ((1u << lg) < upr) lg++;
-    const uint64_t per = lg <= 6 ? 64u >> lg : 1u;                       // rows per wavefront pass
-    const uint64_t blocks = ((pairs + per - 1) / per * 64u + kRnnThreads - 1) / kRnnThreads;
-    hipLaunchKernelGGL(rnn_scatter, dim3((unsigned)(blocks < 65536 ? blocks : 65536)),
-                       dim3(kRnnThreads), 0, (hipStream_t)stream, (const uint8_t *)wk.cand,
-                       (const u32x4 *)list, (const uint32_t *)count, (uint8_t *)status, p.srb, w, upr, lg,
-                       wk.winner);
     if (hipGetLastError() != hipSuccess) return NLB_EDEVICE;
     return NLB_OK;
 }
