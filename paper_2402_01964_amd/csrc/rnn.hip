@@ -28,7 +28,7 @@
 //   gru      where its registers suffice, the weight-stationary form
 //            (rnn_gru_ws: one workgroup per CU keeps the weights in
 //            registers and loops over 32-row tiles of listed rows);
-//            otherwise a workgroup takes a tile of 16, 32 or 64 listed rows
+//            otherwise a workgroup takes tiles of up to three 16-row blocks
 //            and reads the weights from L2 (rnn_gru).  Both build the inputs
 //            in LDS and run both GRU products on bf16 matrix cores; the
 //            gates, the blend with h and the rounding to the status type
@@ -50,28 +50,26 @@
 // as a single term; the weights are bf16 and the products accumulate in fp32.
 //
 // Matrix-core mapping (v_mfma_f32_16x16x32_bf16; lane layout as in
-// aggregate.hip).  Wavefront w computes the output units 16 ub .. 16 ub + 15
-// for ub = w, w + 4, ...; for each it keeps four accumulators per 16-row
-// block -- r and z (input and hidden products summed), the input part of n
-// and the hidden part of n -- so a unit's three gates meet in one lane and
-// the cell finishes without another LDS round trip.  The weight fragments
-// (packed, read from global memory, where the whole weight set stays
-// L2-resident) go through a three-slot register ring, so each k-step's
-// loads are issued two steps before their products.
+// aggregate.hip).  A wavefront computes the output units 16 ub .. 16 ub + 15;
+// it keeps four accumulators per 16-row block -- r and z (input and hidden
+// products summed), the input part of n and the hidden part of n -- so a
+// unit's three gates meet in one lane and the cell finishes without another
+// LDS round trip.  The weight fragments (packed, read from global memory, where
+// the whole weight set stays L2-resident) go through a register ring, so each
+// k-step's loads are issued steps before their products.
 #include <algorithm>
 #include <cstring>
 #include <mutex>
 
 #include "nlb_internal.h"
 #include "nlb_pieces.h"
+#include "nlb_units.h"
 
 namespace {
 
 constexpr int kRnnThreads = 256;
 constexpr uint32_t kGruMetaRows = 1024;           // LDS bytes of the tile's row list (4 words per row)
-constexpr uint32_t kGruLdsBudget = 80 * 1024;     // two workgroups per CU
 constexpr uint32_t kGruLdsMax = 160 * 1024;       // gfx950: LDS of one workgroup at most
-constexpr uint32_t kGruTargetTiles = 1024;      // tiles wanted per launch (counted on 2n rows)
 
 struct ResolveParams {
     const int32_t *src;
@@ -169,10 +167,11 @@ __global__ __launch_bounds__(kMergeThreads) void rnn_resolve_merged(ResolveParam
 struct SelectParams {
     const int32_t *src;
     const int32_t *dst;
+    const uint32_t *t;
     uint32_t n;
     int64_t num_nodes;
     const unsigned long long *winner;
-    u32x4 *list;          // winners, dense: {pair row, self, other, 0}
+    u32x4 *list;          // winners, dense: {pair row, self, other, link time}
     uint32_t *count;
     // The statuses r_other of the winners, staged by list position, so that
     // the GRU pass may overwrite statuses while other tiles are still to be
@@ -235,11 +234,13 @@ __global__ __launch_bounds__(T) void rnn_select(SelectParams p) {
     constexpr int RS = T / T;
     const uint64_t r0 = (uint64_t)blockIdx.x * T;
     int32_t su[RS], sv[RS];
+    uint32_t st[RS];
 #pragma unroll
     for (int q = 0; q < RS; q++) {
         const uint64_t r = min(r0 + q * T + threadIdx.x, 2ull * p.n - 1ull);
         su[q] = p.src[(uint32_t)(r >> 1)];
         sv[q] = p.dst[(uint32_t)(r >> 1)];
+        st[q] = p.t[(uint32_t)(r >> 1)];
     }
     unsigned long long wv[RS];
 #pragma unroll
@@ -270,7 +271,7 @@ __global__ __launch_bounds__(T) void rnn_select(SelectParams p) {
         off = __shfl(off, (int)leader);
         if (win)
             rows[off + (uint32_t)__popcll(mask & ((1ull << lane) - 1ull))] =
-                u32x4{(uint32_t)r, (uint32_t)self, (uint32_t)other, 0u};
+                u32x4{(uint32_t)r, (uint32_t)self, (uint32_t)other, st[q]};
     }
     __syncthreads();
     // The workgroup's place in the list and the list entries, while the first
@@ -296,7 +297,7 @@ struct GruParams {
     const uint32_t *t;
     uint32_t n;
     int64_t num_nodes;
-    const u32x4 *list;                  // winners {pair row, self, other, 0} (select)
+    const u32x4 *list;                  // winners {pair row, self, other, link time} (select)
     const uint32_t *count;
     uint64_t first_eid;                 // arrival index (link-row index) of link 0, or NLB_EID_LAST_BATCH
     const uint32_t *table_status;       // the table's device status words (its link count)
@@ -313,11 +314,11 @@ struct GruParams {
     uint32_t kd, off_e, kx;             // X = [r_other | T-enc | e]: columns [0,kd) [kd,off_e) [off_e,kx)
     uint32_t lo_begin, lo_end;          // X columns with a stored lo plane
     uint32_t h_lo;                      // fp32 statuses: H has a lo plane
-    uint32_t xs, ls, hs;                // LDS row strides (bf16 elements)
-    uint32_t rows;                      // listed rows per tile (16, 32 or 64)
-    uint32_t off_xl, off_h, off_hl;     // LDS byte offsets
-    uint64_t gx_m, gh_m;                // nlb_div_magic(kx / 8), nlb_div_magic(kd / 8)
-    uint64_t gt_m, ge_m;                // nlb_div_magic((off_e - kd) / 8), nlb_div_magic((kx - off_e) / 8)
+    uint32_t xs, ls;                    // LDS row strides (bf16 elements) of the hi and lo planes
+    uint32_t nbmax;                     // 16-row blocks per tile at most
+    uint32_t off_xl;                    // LDS byte offset of the lo plane
+    uint64_t gh_m;                      // nlb_div_magic(kd / 8)
+    uint64_t gt_m, ge_m;                // nlb_div_magic((off_e - kd) / 4), nlb_div_magic((kx - off_e) / 8)
     int32_t s_kind, e_kind;             // piece forms of status / link rows (-1: none applies)
     uint32_t meta;                      // LDS bytes before X: row list, then T-enc w | b (pad32(d_time) each)
     uint32_t ws_lomask;                 // weight-stationary form: bit s set if X k-step s has a lo plane
@@ -371,79 +372,11 @@ __device__ __forceinline__ uint16_t f32_to_bf16_rne(float f) {
     return (uint16_t)((u + 0x7FFFu + ((u >> 16) & 1u)) >> 16);
 }
 
-// acc[g'][rb] += A_rb (16 x 32 blocks of the LDS pair Ah/Al, row stride
-// `as`; the lo plane starts at column lo_b with its own stride `ls`)
-//              * W_g^T for the three gates, over the k-steps kb, kb + 32, ..
-// < ke; g' = g for the r and z gates and g' = NIDX for the n gate.  LO adds
-// the lo-plane products.  The weights come packed (rnn_select): wp points at
-// this lane's word of the fragment (k-step 0, gate 0) of the matrix and unit
-// block; fragment (k-step s, gate g) is 192 s + 64 g words on.
-template <int NB, bool LO, int NIDX>
-__device__ __forceinline__ void gate_seg(f32x4 (&acc)[4][NB], const __bf16 *Ah, const __bf16 *Al,
-                                         uint32_t as, uint32_t ls, uint32_t lo_b, const u32x4 *wp,
-                                         uint32_t kb, uint32_t ke, uint32_t lr, uint32_t lk) {
-    if (kb >= ke) return;
-    const uint32_t last = ke - 32;
-    bf16x8 r0[3], r1[3], r2[3];
-    auto load = [&](bf16x8 (&b)[3], uint32_t k) {
-#pragma unroll
-        for (int g = 0; g < 3; g++) b[g] = __builtin_bit_cast(bf16x8, wp[(k >> 5) * 192u + g * 64u]);
-    };
-    auto step = [&](const bf16x8 (&b)[3], uint32_t k0) {
-        bf16x8 a[NB], al[NB];
-#pragma unroll
-        for (int rb = 0; rb < NB; rb++) a[rb] = *(const bf16x8 *)(Ah + (16u * rb + lr) * as + k0 + lk);
-        if (LO) {
-#pragma unroll
-            for (int rb = 0; rb < NB; rb++)
-                al[rb] = *(const bf16x8 *)(Al + (16u * rb + lr) * ls + (k0 - lo_b) + lk);
-        }
-#pragma unroll
-        for (int rb = 0; rb < NB; rb++)
-#pragma unroll
-            for (int g = 0; g < 3; g++) {
-                const int gi = g == 2 ? NIDX : g;
-                acc[gi][rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[rb], b[g], acc[gi][rb], 0, 0, 0);
-            }
-        if (LO) {
-#pragma unroll
-            for (int rb = 0; rb < NB; rb++)
-#pragma unroll
-                for (int g = 0; g < 3; g++) {
-                    const int gi = g == 2 ? NIDX : g;
-                    acc[gi][rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al[rb], b[g], acc[gi][rb], 0, 0, 0);
-                }
-        }
-        // All LDS reads of the step first, then its products.
-        __builtin_amdgcn_sched_group_barrier(0x0100, LO ? 2 * NB : NB, 0);
-        __builtin_amdgcn_sched_group_barrier(0x0008, LO ? 6 * NB : 3 * NB, 0);
-    };
-    // Three-slot ring: the loads of step k + 64 are issued before the
-    // products of step k (the scheduling barriers keep them there).
-    // Prefetches past the segment re-read its last step (in bounds, unused).
-    load(r0, kb);
-    load(r1, kb + 32 < ke ? kb + 32 : last);
-    uint32_t k0 = kb;
-    for (; k0 + 64 < ke; k0 += 96) {
-        load(r2, k0 + 64);
-        __builtin_amdgcn_sched_barrier(0);
-        step(r0, k0);
-        load(r0, k0 + 96 < ke ? k0 + 96 : last);
-        __builtin_amdgcn_sched_barrier(0);
-        step(r1, k0 + 32);
-        load(r1, k0 + 128 < ke ? k0 + 128 : last);
-        __builtin_amdgcn_sched_barrier(0);
-        step(r2, k0 + 64);
-    }
-    if (k0 < ke) step(r0, k0);
-    if (k0 + 32 < ke) step(r1, k0 + 32);
-}
-
 // One input segment of a tile: `units` pieces of 8 columns, piece u of tile
 // row j = u / g at column c0 = 8 (u - j g), from the row row_of(j) (a valid
 // address for every j < R); store(j, c0, piece) writes it to LDS.  F pieces
 // per thread (of NT) are loaded before any is stored.
-template <int KIND, int F, uint32_t NT = kRnnThreads, typename RowOf, typename Store>
+template <int KIND, int F, uint32_t NT, typename RowOf, typename Store>
 __device__ __forceinline__ void fill_seg(uint32_t units, uint32_t g, uint64_t g_m, uint32_t dim, RowOf row_of,
                                          Store store) {
     for (uint32_t base = threadIdx.x; base < units; base += NT * F) {
@@ -465,284 +398,480 @@ __device__ __forceinline__ void fill_seg(uint32_t units, uint32_t g, uint64_t g_
     }
 }
 
-// A tile's inputs X = [r_other | T-enc(t) | e] and H = r_self for tile rows
-// j < m (rows m .. 16 NB - 1 are written as zeros), as bf16 hi planes at Xh
-// and Hh and lo planes at Xl (columns [lo_begin, lo_end)) and Hl (fp32
-// statuses), with row strides xs, ls, hs -- in LDS or in global memory.
-// m_row .. m_t are the tile rows' list entries and link times, others their
-// staged rows r_other, s_tw / s_tb
-// the zero-padded time-encoding parameters (LDS).  The caller synchronises.
-template <int NB>
-__device__ __forceinline__ void gru_fill(const GruParams &p, uint32_t m, const uint32_t *m_row,
-                                         const int32_t *m_self, const uint8_t *others, const float *m_t,
-                                         const float *s_tw, const float *s_tb, __bf16 *Xh, __bf16 *Xl,
-                                         __bf16 *Hh, __bf16 *Hl, uint32_t xs, uint32_t ls, uint32_t hs) {
-    const uint64_t first_eid = first_eid_of(p);
-    constexpr uint32_t R = 16 * NB;
-    // Input units (8 columns each) whose loads a thread keeps in flight
-    // together (generic path): about all of its units for the common widths.
-    constexpr int kFill = NB == 4 ? 12 : (NB == 2 ? 8 : 4);
-    const uint32_t tid = threadIdx.x;
-    if (p.s_kind >= 0 && (p.e_kind >= 0 || p.kx == p.off_e)) {
-        // Inputs segment by segment, each with its rows' fixed piece form:
-        // statuses (H = r_self, then X's r_other), the time encoding, link
-        // rows.  Rows m .. R-1 of the tile read row 0 of the list and are
-        // stored as zeros.
-        const uint32_t d = p.d, gh = p.kd / 8, us = R * gh;
-        auto status_fill = [&](auto kind) {
-            constexpr int K = decltype(kind)::value;
-            // Pieces u < us: H rows (self); us <= u < 2 us: X rows (other),
-            // by tile row j = u / gh over 2R rows.
-            fill_seg<K, 8>(
-                2u * us, gh, p.gh_m, d,
-                [&](uint32_t jj) {
-                    const uint32_t j = jj < R ? jj : jj - R, jm = j < m ? j : 0;
-                    return jj < R ? (const uint8_t *)p.st + (size_t)m_self[jm] * p.srb : others + (size_t)jm * p.srb;
-                },
-                [&](uint32_t jj, uint32_t c0, const Piece8<K> &pc) {
-                    const uint32_t j = jj < R ? jj : jj - R;
-                    const bool ok = j < m;
-                    if constexpr (K == kF32Vec) {
-                        float v[8];
-                        piece_floats<K>(pc, d, c0, ok, v);
-                        if (jj < R)
-                            store_split8(v, Hh + (size_t)j * hs + c0, Hl + (size_t)j * hs + c0);
-                        else
-                            store_split8(v, Xh + (size_t)j * xs + c0,
-                                         Xl + (size_t)j * ls + (c0 - p.lo_begin));
-                    } else {
-                        const u32x4 w = piece_bf16_bits<K>(pc, d, c0, ok);
-                        *(u32x4 *)(jj < R ? Hh + (size_t)j * hs + c0 : Xh + (size_t)j * xs + c0) = w;
-                    }
-                });
-        };
-        if (p.s_kind == kF32Vec)
-            status_fill(std::integral_constant<int, kF32Vec>{});
-        else if (p.s_kind == kBf16Word)
-            status_fill(std::integral_constant<int, kBf16Word>{});
-        else
-            status_fill(std::integral_constant<int, kBf16Vec>{});
+// The tiled GRU pass (rnn_gru).  A persistent workgroup of eight wavefronts
+// takes the 16-row blocks blockIdx.x, blockIdx.x + gridDim.x, ... of the
+// winner list, up to p.nbmax of them as one tile: with one workgroup per CU the
+// blocks spread evenly whatever the winner count, which the host does not
+// know, turns out to be, and a block's list entries can be requested before
+// the count arrives.  (Tiles of consecutive rows, sized by the host for all 2n
+// pair rows: 10 000 links gave 660 tiles of 16 rows, each of which reads
+// all weights, 380 KB, from L2; here each CU reads them once per tile of 32 or
+// 48 rows.)
+//
+// What bounds it: at small batches the chain of dependent round trips (count
+// and list, the tile's rows, the weights), so whatever a step needs is
+// requested as early as it is known: the first weight fragments before the
+// list arrives, all of a thread's status and link-row pieces together, the
+// time encoding computed while they are on their way, biases and h values
+// before the products; and the k-steps of both products run as one sequence
+// through a ring of kGruRing steps of weight fragments that goes on into the
+// next unit block's (a ring per segment refilled four times per unit block).
+// Wavefront w computes unit block w (w + 8, ... of statuses wider than 128);
+// with at most four unit blocks the row blocks are split among the
+// wavefronts as well.  At larger ones the weights' way from L2 (a CU's 64
+// bytes a clock) and the matrix instructions bound it.
+//
+// Measured: 600 links, fp32 statuses of 100, fp32 link rows of 172:
+// 15.0 -> 11.6 us; 10 000 links, bf16 link rows of 186: 25.6 -> 20.6 us (the
+// form of 256-thread workgroups, a tile each, that this one took the place of).
+constexpr int kGruRing = 4;
+constexpr int kGruBlocks = 3;      // row blocks of a tile at most
 
-        // Time encoding cos(w_k t + b_k) of each row's link time.
-        const uint32_t gt = (p.off_e - p.kd) / 8;
-        for (uint32_t u = tid; u < R * gt; u += kRnnThreads) {
-            const uint32_t j = nlb_div(u, p.gt_m), k = (u - j * gt) * 8u;
-            const float tf = m_t[j < m ? j : 0];
-            const f32x4 w0 = *(const f32x4 *)(s_tw + k), w1 = *(const f32x4 *)(s_tw + k + 4);
-            const f32x4 b0 = *(const f32x4 *)(s_tb + k), b1 = *(const f32x4 *)(s_tb + k + 4);
-            float v[8];
-#pragma unroll
-            for (int i = 0; i < 4; i++) {
-                v[i] = cos_fp32(__builtin_fmaf(w0[i], tf, b0[i]));
-                v[4 + i] = cos_fp32(__builtin_fmaf(w1[i], tf, b1[i]));
-            }
-#pragma unroll
-            for (int i = 0; i < 8; i++) v[i] = (j < m && k + i < p.d_time) ? v[i] : 0.0f;
-            store_split8(v, Xh + (size_t)j * xs + p.kd + k, Xl + (size_t)j * ls + (p.kd + k - p.lo_begin));
-        }
+// The forms of a row matrix here: rows of at least one 16-byte unit at 4-byte
+// alignment are read in units (nlb_units.h), others element by element.
+constexpr int kSegNone = 0, kSegBf16 = 1, kSegF32 = 2, kSegAny = 3;
 
-        // Link rows (rows at or past edge_rows are zeros).
-        if (p.kx > p.off_e) {
-            const uint32_t ge = (p.kx - p.off_e) / 8;
-            auto edge_fill = [&](auto kind) {
-                constexpr int K = decltype(kind)::value;
-                auto eid_of = [&](uint32_t j) { return first_eid + (m_row[j < m ? j : 0] >> 1); };
-                fill_seg<K, 8>(
-                    R * ge, ge, p.ge_m, p.e_dim,
-                    [&](uint32_t j) {
-                        const uint64_t e = eid_of(j);
-                        return p.efeat + (size_t)(e < (uint64_t)p.edge_rows ? e : 0u) * p.erb;
-                    },
-                    [&](uint32_t j, uint32_t c0, const Piece8<K> &pc) {
-                        const bool ok = j < m && eid_of(j) < (uint64_t)p.edge_rows;
-                        if constexpr (K == kF32Vec) {
-                            float v[8];
-                            piece_floats<K>(pc, p.e_dim, c0, ok, v);
-                            store_split8(v, Xh + (size_t)j * xs + p.off_e + c0,
-                                         Xl + (size_t)j * ls + (p.off_e + c0 - p.lo_begin));
-                        } else {
-                            *(u32x4 *)(Xh + (size_t)j * xs + p.off_e + c0) =
-                                piece_bf16_bits<K>(pc, p.e_dim, c0, ok);
-                        }
-                    });
-            };
-            if (p.e_kind == kF32Vec)
-                edge_fill(std::integral_constant<int, kF32Vec>{});
-            else if (p.e_kind == kBf16Word)
-                edge_fill(std::integral_constant<int, kBf16Word>{});
-            else
-                edge_fill(std::integral_constant<int, kBf16Vec>{});
-        }
-    } else {
-
-    // Inputs: X = [r_other | T-enc(t) | e] and H = r_self; rows m .. R-1
-    // are zero.  Units of 8 columns: X's R * kx / 8 first, then H's; the
-    // loads of kFill units per thread are in flight together.
-    const uint32_t gx = p.kx / 8, gh = p.kd / 8;
-    const uint32_t ux = R * gx;
-    const uint32_t ut = ux + R * gh;
-    for (uint32_t base = tid; base < ut; base += kRnnThreads * kFill) {
-        float v[kFill][8];
-#pragma unroll
-        for (int f = 0; f < kFill; f++) {
-            const uint32_t u = base + f * kRnnThreads;
-#pragma unroll
-            for (int i = 0; i < 8; i++) v[f][i] = 0.0f;
-            if (u >= ut) continue;
-            if (u >= ux) {
-                const uint32_t j = nlb_div(u - ux, p.gh_m);
-                const uint32_t c0 = (u - ux - j * gh) * 8;
-                if (j < m) load8(p.st + (size_t)m_self[j] * p.srb, p.d, p.s_bf16, p.s_vec, c0, v[f]);
-                continue;
-            }
-            const uint32_t j = nlb_div(u, p.gx_m);
-            const uint32_t c0 = (u - j * gx) * 8;
-            if (j >= m) continue;
-            const uint32_t link = m_row[j] >> 1;
-            if (c0 < p.kd) {
-                load8(others + (size_t)j * p.srb, p.d, p.s_bf16, p.o_vec, c0, v[f]);
-            } else if (c0 < p.off_e) {
-                const uint32_t k = c0 - p.kd;
-                const float tf = (float)p.t[link];
-                float wk[8], bk[8];
-                if (p.t_vec && k + 8 <= p.d_time) {
-                    const f32x4 w0 = *(const f32x4 *)(p.tw + k), w1 = *(const f32x4 *)(p.tw + k + 4);
-                    const f32x4 b0 = *(const f32x4 *)(p.tb + k), b1 = *(const f32x4 *)(p.tb + k + 4);
-#pragma unroll
-                    for (int i = 0; i < 4; i++) {
-                        wk[i] = w0[i];
-                        wk[4 + i] = w1[i];
-                        bk[i] = b0[i];
-                        bk[4 + i] = b1[i];
-                    }
-                } else {
-#pragma unroll
-                    for (int i = 0; i < 8; i++) {
-                        wk[i] = k + i < p.d_time ? p.tw[k + i] : 0.0f;
-                        bk[i] = k + i < p.d_time ? p.tb[k + i] : 0.0f;
-                    }
-                }
-#pragma unroll
-                for (int i = 0; i < 8; i++)
-                    if (k + i < p.d_time) v[f][i] = cos_fp32(__builtin_fmaf(wk[i], tf, bk[i]));
-            } else {
-                const uint64_t e = first_eid + link;
-                if (e < (uint64_t)p.edge_rows)
-                    load8(p.efeat + (size_t)e * p.erb, p.e_dim, p.e_bf16, p.e_vec, c0 - p.off_e, v[f]);
-            }
-        }
-#pragma unroll
-        for (int f = 0; f < kFill; f++) {
-            const uint32_t u = base + f * kRnnThreads;
-            if (u >= ut) continue;
-            if (u >= ux) {
-                const uint32_t j = nlb_div(u - ux, p.gh_m);
-                const uint32_t c0 = (u - ux - j * gh) * 8;
-                if (p.h_lo)
-                    store_split8(v[f], Hh + (size_t)j * hs + c0, Hl + (size_t)j * hs + c0);
-                else
-                    store_hi8(v[f], Hh + (size_t)j * hs + c0);
-                continue;
-            }
-            const uint32_t j = nlb_div(u, p.gx_m);
-            const uint32_t c0 = (u - j * gx) * 8;
-            if (c0 >= p.lo_begin && c0 < p.lo_end)
-                store_split8(v[f], Xh + (size_t)j * xs + c0, Xl + (size_t)j * ls + (c0 - p.lo_begin));
-            else
-                store_hi8(v[f], Xh + (size_t)j * xs + c0);
-        }
-    }
-    }
-
+inline int seg_form(uint32_t dim, uint32_t row_bytes, const void *base, bool bf16) {
+    if (row_bytes % 4 || (uintptr_t)base % 4 || dim < (bf16 ? 8u : 4u)) return kSegAny;
+    return bf16 ? kSegBf16 : kSegF32;
 }
 
-template <int NB>
-__global__ __launch_bounds__(kRnnThreads) void rnn_gru(GruParams p) {
+// Columns c .. c + 7 of a row, as loaded.
+template <int FORM>
+struct SegPiece {
+    u32x4 w[FORM == kSegF32 ? 2 : 1];
+};
+
+template <int FORM>
+__device__ __forceinline__ void seg_request(const uint8_t *row, uint32_t dim, uint32_t c, SegPiece<FORM> &r) {
+    if constexpr (FORM == kSegF32) {
+        r.w[0] = *(const u32x4_at4 *)(row + 4u * unit_start(c, dim, 4));
+        r.w[1] = *(const u32x4_at4 *)(row + 4u * unit_start(c + 4u, dim, 4));
+    } else {
+        r.w[0] = *(const u32x4_at4 *)(row + 2u * unit_start(c, dim, 8));
+    }
+}
+
+// Unit c (4 fp32 or 8 bf16 elements) in column order, zero past the width:
+// the words move down by those that a cut unit shares with the unit before.
+template <int FORM>
+__device__ __forceinline__ u32x4 seg_unit(u32x4 w, uint32_t dim, uint32_t c) {
+    constexpr uint32_t U = FORM == kSegF32 ? 4 : 8;
+    const uint32_t k = c < dim ? unit_shared(c, dim, U) * 4u / U : 4u;
+    if (k) {
+        if (k & 1u) w = u32x4{w[1], w[2], w[3], 0u};
+        if (k & 2u) w = u32x4{w[2], w[3], 0u, 0u};
+        if (k & 4u) w = u32x4(0u);
+    }
+    return w;
+}
+
+// The piece, written to LDS (fp32 as hi + lo), zeros where `ok` is false.
+template <int FORM>
+__device__ __forceinline__ void seg_store(const SegPiece<FORM> &r, uint32_t dim, uint32_t c, bool ok, __bf16 *hi,
+                                          __bf16 *lo) {
+    if constexpr (FORM == kSegF32) {
+        const u32x4 a = seg_unit<FORM>(r.w[0], dim, c), b = seg_unit<FORM>(r.w[1], dim, c + 4u);
+        float v[8];
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            v[i] = ok ? __uint_as_float(a[i]) : 0.0f;
+            v[4 + i] = ok ? __uint_as_float(b[i]) : 0.0f;
+        }
+        store_split8(v, hi, lo);
+    } else {
+        const u32x4 a = seg_unit<FORM>(r.w[0], dim, c);
+        *(u32x4 *)hi = ok ? a : u32x4(0u);
+    }
+}
+
+// A tile in LDS: hi plane [rows][xs], columns [r_other | T-enc | e | r_self],
+// and the lo plane [rows][ls] of X's columns [lo_begin, lo_end), then (fp32
+// statuses) of r_self.
+struct GruTile {
+    uint32_t *m_row;      // tile row j's pair row
+    int32_t *m_self;      // its node
+    float *m_t;           // its link's time, as fp32
+    float *s_tw, *s_tb;   // time-encoding parameters, zero-padded to 32
+    __bf16 *hi, *lo;
+    uint32_t m;           // valid rows (the last block's may be fewer than 16)
+    uint32_t b0, stride;  // list block of row block rb: b0 + rb * stride
+};
+
+// cos of an fp32 argument as cos_fp32, with the wide arguments' reduction
+// inline (a call would take registers from the whole kernel).
+__device__ __forceinline__ float cos_inline(float x) {
+    float c = cos_fp32_small(x);
+    if (!(fabsf(x) < kCosFastLimit)) c = cos_fp32_exact_wide(x);
+    return c;
+}
+
+// The thread's index, opaque to the compiler: what follows from it is then
+// computed where it is used, and not ahead of the tile loop for every case of
+// its switches (which spilled 300 registers).
+__device__ __forceinline__ uint32_t thread_here() {
+    uint32_t t = threadIdx.x;
+    asm volatile("" : "+v"(t));
+    return t;
+}
+
+// The time encoding of the tile's rows, four columns a unit.
+template <int NT, int NB>
+__device__ __forceinline__ void gru_encode(const GruParams &p, const GruTile &T) {
+    const uint32_t gt = (p.off_e - p.kd) / 4u;
+    for (uint32_t u = thread_here(); u < 16u * NB * gt; u += NT) {
+        const uint32_t j = nlb_div(u, p.gt_m), k = (u - j * gt) * 4u;
+        float v[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+        if (k < p.d_time) {
+            const float tf = T.m_t[j < T.m ? j : 0];
+            const f32x4 w = *(const f32x4 *)(T.s_tw + k), b = *(const f32x4 *)(T.s_tb + k);
+#pragma unroll
+            for (int i = 0; i < 4; i++) v[i] = k + i < p.d_time ? cos_inline(__builtin_fmaf(w[i], tf, b[i])) : 0.0f;
+        }
+        typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+        bf16x4 h, l;
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            h[i] = (__bf16)v[i];
+            l[i] = (__bf16)(v[i] - (float)h[i]);
+        }
+        *(bf16x4 *)(T.hi + (size_t)j * p.xs + p.kd + k) = h;
+        *(bf16x4 *)(T.lo + (size_t)j * p.ls + (p.kd + k - p.lo_begin)) = l;
+    }
+}
+
+// A tile's inputs, rows in 16-byte units.  Tile rows past T.m read row 0 and
+// keep its values: their results are not written.
+template <int NT, int NB, int SF, int EF>
+__device__ __forceinline__ void gru_fill(const GruParams &p, const GruTile &T, uint64_t first_eid) {
     constexpr uint32_t R = 16 * NB;
-    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
-    uint32_t *m_row = (uint32_t *)smem;          // pair row of tile row j
-    int32_t *m_self = (int32_t *)(m_row + 64);
-    float *m_t = (float *)(m_self + 64);         // its link's time, as fp32
-    float *s_tw = (float *)(smem + kGruMetaRows), *s_tb = s_tw + ((p.d_time + 31u) & ~31u);
-    __bf16 *Xh = (__bf16 *)(smem + p.meta);
-    __bf16 *Xl = (__bf16 *)(smem + p.off_xl);
-    __bf16 *Hh = (__bf16 *)(smem + p.off_h);
-    __bf16 *Hl = (__bf16 *)(smem + p.off_hl);
-
-    const uint32_t tid = threadIdx.x;
-    const uint32_t lane = tid & 63, wave = tid >> 6;
-    const uint32_t count = *p.count;
-    const uint64_t j0 = (uint64_t)blockIdx.x * R;
-    if (j0 >= count) return;
-    const uint32_t m = (uint32_t)min((uint64_t)R, (uint64_t)count - j0);
-    if (tid < m) {
-        const u32x4 e = p.list[j0 + tid];
-        m_row[tid] = e[0];
-        m_self[tid] = (int32_t)e[1];
-        p.winner[e[1]] = 0ull;
-        m_t[tid] = (float)p.t[e[0] >> 1];
-    }
-    for (uint32_t u = tid; u < ((p.d_time + 31u) & ~31u); u += kRnnThreads) {
-        s_tw[u] = u < p.d_time ? p.tw[u] : 0.0f;
-        s_tb[u] = u < p.d_time ? p.tb[u] : 0.0f;
-    }
-    __syncthreads();
-
-    gru_fill<NB>(p, m, m_row, m_self, p.stage + j0 * p.srb, m_t, s_tw, s_tb, Xh, Xl, Hh, Hl, p.xs, p.ls, p.hs);
-    __syncthreads();
-
-    const uint32_t d = p.d;
-    const uint32_t units = (d + 15) / 16;
-    const uint32_t lr = lane & 15, lk = (lane >> 4) * 8;
-    for (uint32_t ub = wave; ub < units; ub += kRnnThreads / 64) {
-        const uint32_t j = 16 * ub + lr;
-        const uint32_t jr = j < d ? j : d - 1;   // rows past d are read, never used
-        // The epilogue's h values, loaded before the products so that
-        // their latency overlaps them.
-        float hv[NB][4];
+    const uint32_t tid = thread_here(), gh = p.kd / 8, us = 2u * R * gh;
+    // Status pieces: the first R rows r_self, the next R rows r_other.
+    SegPiece<SF> sp[NB];
+    auto s_at = [&](uint32_t u, uint32_t &jj, uint32_t &c) {
+        jj = nlb_div(u, p.gh_m);
+        c = (u - jj * gh) * 8u;
+    };
+    auto s_request = [&](uint32_t base) {
 #pragma unroll
-        for (int rb = 0; rb < NB; rb++)
+        for (int f = 0; f < NB; f++) {
+            uint32_t jj, c;
+            s_at(min(base + f * NT, us - 1u), jj, c);
+            const uint32_t j = jj < R ? jj : jj - R, jm = j < T.m ? j : 0u;
+            const uint8_t *row = jj < R ? p.st + (size_t)T.m_self[jm] * p.srb
+                                        : p.stage + (((size_t)T.b0 + (jm >> 4) * T.stride) * 16u + (jm & 15u)) * p.srb;
+            seg_request<SF>(row, p.d, c, sp[f]);
+        }
+    };
+    auto s_store = [&](uint32_t base) {
 #pragma unroll
-            for (int i = 0; i < 4; i++) {
-                const uint32_t row = 16u * rb + 4u * (lane >> 4) + i;
-                const uint8_t *srow = p.st + (size_t)m_self[row < m ? row : 0] * p.srb;
-                hv[rb][i] = p.s_bf16 ? bf16_bits_to_float(((const uint16_t *)srow)[jr])
-                                     : ((const float *)srow)[jr];
+        for (int f = 0; f < NB; f++) {
+            const uint32_t u = base + f * NT;
+            if (u >= us) break;
+            uint32_t jj, c;
+            s_at(u, jj, c);
+            const bool self = jj < R;
+            const uint32_t j = self ? jj : jj - R;
+            seg_store<SF>(sp[f], p.d, c, true, T.hi + (size_t)j * p.xs + (self ? p.kx : 0u) + c,
+                          T.lo + (size_t)j * p.ls + (self ? p.lo_end - p.lo_begin : 0u) + c);
+        }
+    };
+    const uint32_t ge = (p.kx - p.off_e) / 8, ue = R * ge;
+    SegPiece<EF> ep[NB];
+    auto e_at = [&](uint32_t u, uint32_t &j, uint32_t &c, uint64_t &e) {
+        j = nlb_div(u, p.ge_m);
+        c = (u - j * ge) * 8u;
+        e = first_eid + (T.m_row[j < T.m ? j : 0u] >> 1);
+    };
+    auto e_request = [&](uint32_t base) {
+#pragma unroll
+        for (int f = 0; f < NB; f++) {
+            uint32_t j, c;
+            uint64_t e;
+            e_at(min(base + f * NT, ue - 1u), j, c, e);
+            seg_request<EF>(p.efeat + (size_t)(e < (uint64_t)p.edge_rows ? e : 0u) * p.erb, p.e_dim, c, ep[f]);
+        }
+    };
+    auto e_store = [&](uint32_t base) {
+#pragma unroll
+        for (int f = 0; f < NB; f++) {
+            const uint32_t u = base + f * NT;
+            if (u >= ue) break;
+            uint32_t j, c;
+            uint64_t e;
+            e_at(u, j, c, e);
+            seg_store<EF>(ep[f], p.e_dim, c, e < (uint64_t)p.edge_rows, T.hi + (size_t)j * p.xs + p.off_e + c,
+                          T.lo + (size_t)j * p.ls + (p.off_e + c - p.lo_begin));
+        }
+    };
+    s_request(tid);
+    if constexpr (EF != kSegNone) e_request(tid);
+    gru_encode<NT, NB>(p, T);
+    s_store(tid);
+    if constexpr (EF != kSegNone) e_store(tid);
+    for (uint32_t base = tid + NB * NT; base < us; base += NB * NT) {
+        s_request(base);
+        s_store(base);
+    }
+    if constexpr (EF != kSegNone)
+        for (uint32_t base = tid + NB * NT; base < ue; base += NB * NT) {
+            e_request(base);
+            e_store(base);
+        }
+}
+
+// The same for rows that have no unit form: eight columns a unit, element by
+// element.
+template <int NT, int NB>
+__device__ __forceinline__ void gru_fill_any(const GruParams &p, const GruTile &T, uint64_t first_eid) {
+    constexpr uint32_t R = 16 * NB;
+    const uint32_t gh = p.kd / 8, ge = (p.kx - p.off_e) / 8, us = 2u * R * gh, ut = us + R * ge;
+    gru_encode<NT, NB>(p, T);
+    for (uint32_t u = thread_here(); u < ut; u += NT) {
+        float v[8];
+#pragma unroll
+        for (int i = 0; i < 8; i++) v[i] = 0.0f;
+        if (u < us) {
+            const uint32_t jj = nlb_div(u, p.gh_m), c = (u - jj * gh) * 8u;
+            const bool self = jj < R;
+            const uint32_t j = self ? jj : jj - R, jm = j < T.m ? j : 0u;
+            if (self)
+                load8(p.st + (size_t)T.m_self[jm] * p.srb, p.d, p.s_bf16, p.s_vec, c, v);
+            else
+                load8(p.stage + (((size_t)T.b0 + (jm >> 4) * T.stride) * 16u + (jm & 15u)) * p.srb, p.d, p.s_bf16,
+                      p.o_vec, c, v);
+            __bf16 *hi = T.hi + (size_t)j * p.xs + (self ? p.kx : 0u) + c;
+            if (p.h_lo)
+                store_split8(v, hi, T.lo + (size_t)j * p.ls + (self ? p.lo_end - p.lo_begin : 0u) + c);
+            else
+                store_hi8(v, hi);
+        } else {
+            const uint32_t j = nlb_div(u - us, p.ge_m), c = (u - us - j * ge) * 8u;
+            const uint64_t e = first_eid + (T.m_row[j < T.m ? j : 0u] >> 1);
+            if (e < (uint64_t)p.edge_rows) load8(p.efeat + (size_t)e * p.erb, p.e_dim, p.e_bf16, p.e_vec, c, v);
+            __bf16 *hi = T.hi + (size_t)j * p.xs + p.off_e + c;
+            if (p.off_e + c < p.lo_end)
+                store_split8(v, hi, T.lo + (size_t)j * p.ls + (p.off_e + c - p.lo_begin));
+            else
+                store_hi8(v, hi);
+        }
+    }
+}
+
+// Unit block ub of row blocks rb0 .. rb0 + NB - 1 of the tile: both products,
+// the gates, the new statuses.  The ring holds the first kGruRing k-steps'
+// weight fragments (of `wp`), and at the end those of `wnext`.
+template <int NB, int SF, int EF>
+__device__ __forceinline__ void gru_units(const GruParams &p, const GruTile &T, u32x4 (&ring)[kGruRing][3],
+                                          const u32x4 *wp, const u32x4 *wnext, bool more, uint32_t ub, uint32_t rb0) {
+    const uint32_t lane = thread_here() & 63u, lr = lane & 15u, lk = (lane >> 4) * 8u;
+    const uint32_t d = p.d, j = 16u * ub + lr, jr = j < d ? j : d - 1u;   // rows past d are read, never used
+    // The gate biases and the h values of the blend, requested here and not
+    // touched before the products are done.
+    float bi[3], bh[3];
+#pragma unroll
+    for (int g = 0; g < 3; g++) {
+        bi[g] = p.b_ih[g * d + jr];
+        bh[g] = p.b_hh[g * d + jr];
+    }
+    const bool bf = SF == kSegAny ? p.s_bf16 != 0u : SF == kSegBf16;
+    uint32_t hv[NB][4];
+#pragma unroll
+    for (int rb = 0; rb < NB; rb++) {
+        const uint8_t *srow[4];
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            const uint32_t row = 16u * (rb0 + rb) + 4u * (lane >> 4) + i;
+            srow[i] = p.st + (size_t)T.m_self[row < T.m ? row : 0u] * p.srb;
+        }
+#pragma unroll
+        for (int i = 0; i < 4; i++) hv[rb][i] = bf ? ((const uint16_t *)srow[i])[jr] : ((const uint32_t *)srow[i])[jr];
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    f32x4 acc[4][NB];   // r, z, input part of n, hidden part of n
+#pragma unroll
+    for (int g = 0; g < 4; g++)
+#pragma unroll
+        for (int rb = 0; rb < NB; rb++) acc[g][rb] = f32x4(0.0f);
+    const uint32_t kxm = p.kx / 32u, S = (p.kx + p.kd) / 32u;
+    const uint32_t lb = p.lo_begin / 32u, le = p.lo_end / 32u;
+    const __bf16 *Ah = T.hi + (16u * rb0 + lr) * p.xs + lk, *Al = T.lo + (16u * rb0 + lr) * p.ls + lk;
+    // Steps s .. e - 1, all with a lo plane (its column of step s: 32 c) or all
+    // without, in groups of kGruRing: a whole group has no branches.
+    auto segment = [&](auto with_lo, auto n_index, uint32_t s, uint32_t e, uint32_t c) {
+        constexpr bool LO = decltype(with_lo)::value;
+        constexpr int NI = decltype(n_index)::value;
+        while (s < e) {
+            const uint32_t n = min((uint32_t)kGruRing, e - s), next = s + n;
+            // What the ring takes next: the steps from `next` on, after the last
+            // one the next unit block's (with none to come, a fragment just read).
+            const bool in = next < S;
+            const u32x4 *from = in ? wp + next * 192u : (more ? wnext : wp + (S - 1u) * 192u);
+            const uint32_t top = in ? S - 1u - next : (more ? S - 1u : 0u);
+            bf16x8 a[2][NB], al[2][NB];
+            auto read = [&](int i) {
+#pragma unroll
+                for (int rb = 0; rb < NB; rb++) {
+                    a[i & 1][rb] = *(const bf16x8 *)(Ah + 16u * rb * p.xs + 32u * (s + i));
+                    if constexpr (LO) al[i & 1][rb] = *(const bf16x8 *)(Al + 16u * rb * p.ls + 32u * (c + i));
+                }
+            };
+            auto products = [&](int i) {
+#pragma unroll
+                for (int l = 0; l < (LO ? 2 : 1); l++)
+#pragma unroll
+                    for (int rb = 0; rb < NB; rb++)
+#pragma unroll
+                        for (int g = 0; g < 3; g++) {
+                            f32x4 &to = acc[g == 2 ? NI : g][rb];
+                            to = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                                l ? al[i & 1][rb] : a[i & 1][rb], __builtin_bit_cast(bf16x8, ring[i][g]), to, 0, 0, 0);
+                        }
+            };
+            auto refill = [&](int i) {
+                const u32x4 *f = from + min((uint32_t)i, top) * 192u;
+#pragma unroll
+                for (int g = 0; g < 3; g++) ring[i][g] = f[g * 64 + lane];
+            };
+            if (n == (uint32_t)kGruRing) {
+                read(0);
+#pragma unroll
+                for (int i = 0; i < kGruRing; i++) {
+                    if (i + 1 < kGruRing) read(i + 1);
+                    products(i);
+                    refill(i);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < kGruRing; i++) {
+                    if ((uint32_t)i < n) {
+                        read(i);
+                        products(i);
+                    }
+                    refill(i);
+                }
             }
-        f32x4 acc[4][NB];   // r, z, input part of n, hidden part of n
+            s = next;
+            c += n;
+        }
+    };
+    const std::true_type lo;
+    const std::false_type no;
+    const std::integral_constant<int, 2> x;
+    const std::integral_constant<int, 3> h;
+    if constexpr (SF != kSegF32) segment(no, x, 0u, lb, 0u);
+    segment(lo, x, lb, le, 0u);
+    if constexpr (EF == kSegBf16 || SF == kSegAny) segment(no, x, le, kxm, 0u);
+    if (SF == kSegF32 || (SF == kSegAny && p.h_lo))
+        segment(lo, h, kxm, S, le - lb);
+    else
+        segment(no, h, kxm, S, 0u);
+    const uint32_t row4 = ((thread_here() & 63u) >> 4) * 4u;
+    if (j >= d) return;
 #pragma unroll
-        for (int g = 0; g < 4; g++)
+    for (int rb = 0; rb < NB; rb++)
 #pragma unroll
-            for (int rb = 0; rb < NB; rb++) acc[g][rb] = f32x4(0.0f);
-        const u32x4 *wx = p.wpack + (size_t)ub * ((p.kx + p.kd) / 32u) * 192u + lane;
-        gate_seg<NB, false, 2>(acc, Xh, Xl, p.xs, p.ls, p.lo_begin, wx, 0, p.lo_begin, lr, lk);
-        gate_seg<NB, true, 2>(acc, Xh, Xl, p.xs, p.ls, p.lo_begin, wx, p.lo_begin, p.lo_end, lr, lk);
-        gate_seg<NB, false, 2>(acc, Xh, Xl, p.xs, p.ls, p.lo_begin, wx, p.lo_end, p.kx, lr, lk);
-        const u32x4 *wh = wx + (p.kx / 32u) * 192u;
-        if (p.h_lo)
-            gate_seg<NB, true, 3>(acc, Hh, Hl, p.hs, p.hs, 0, wh, 0, p.kd, lr, lk);
-        else
-            gate_seg<NB, false, 3>(acc, Hh, Hl, p.hs, p.hs, 0, wh, 0, p.kd, lr, lk);
-        if (j >= d) continue;
-        const float br = p.b_ih[j] + p.b_hh[j];
-        const float bz = p.b_ih[d + j] + p.b_hh[d + j];
-        const float bin = p.b_ih[2 * d + j];
-        const float bhn = p.b_hh[2 * d + j];
+        for (int i = 0; i < 4; i++) {
+            const uint32_t row = 16u * (rb0 + rb) + row4 + i;
+            if (row >= T.m) continue;
+            const float hval = bf ? bf16_bits_to_float(hv[rb][i]) : __uint_as_float(hv[rb][i]);
+            const float rg = sigmoid_f32(acc[0][rb][i] + (bi[0] + bh[0]));
+            const float zg = sigmoid_f32(acc[1][rb][i] + (bi[1] + bh[1]));
+            const float ng = tanh_f32(acc[2][rb][i] + bi[2] + rg * (acc[3][rb][i] + bh[2]));
+            const float out = (1.0f - zg) * ng + zg * hval;
+            uint8_t *srow = p.st + (size_t)T.m_self[row] * p.srb;
+            if (bf)
+                ((uint16_t *)srow)[j] = f32_to_bf16_rne(out);
+            else
+                ((float *)srow)[j] = out;
+        }
+}
+
+template <int NT, int SF, int EF>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void rnn_gru(GruParams p) {
+    constexpr uint32_t kWaves = NT / 64;
+    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+    GruTile T;
+    T.m_row = (uint32_t *)smem;
+    T.m_self = (int32_t *)(T.m_row + 64);
+    T.m_t = (float *)(T.m_self + 64);
+    const uint32_t tpad = (p.d_time + 31u) & ~31u;
+    T.s_tw = (float *)(smem + kGruMetaRows);
+    T.s_tb = T.s_tw + tpad;
+    T.hi = (__bf16 *)(smem + p.meta);
+    T.lo = (__bf16 *)(smem + p.off_xl);
+    T.stride = gridDim.x;
+
+    const uint32_t tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63u;
+    const uint32_t units = (p.d + 15u) / 16u, S = (p.kx + p.kd) / 32u;
+    // With fewer unit blocks than wavefronts, `split` groups of wavefronts
+    // share a tile's row blocks; `wave` is unit block ub of group `part`.
+    const uint32_t split = units < kWaves ? kWaves / units : 1u;
+    const uint32_t part = split > 1u ? wave / units : 0u, ub0 = split > 1u ? wave - part * units : wave;
+    const bool works = part < split && ub0 < units;
+    const u32x4 *w0 = p.wpack + (size_t)(works ? ub0 : 0u) * S * 192u;
+
+    // The first blocks' list entries (entries past the list are not used; the
+    // array has 2n of them), the first weight fragments and the time-encoding
+    // parameters, all requested before the winner count is used.
+    auto list_entry = [&](uint32_t k0) {
+        const uint64_t pos = ((uint64_t)blockIdx.x + (uint64_t)(k0 + ((tid & 63u) >> 4)) * T.stride) * 16u + (tid & 15u);
+        return p.list[min(pos, 2u * (uint64_t)p.n - 1u)];
+    };
+    u32x4 ent = list_entry(0u);   // (by every wavefront; the first one's are used)
+    const uint32_t count = *p.count;
+    const uint64_t first_eid = first_eid_of(p);
+    u32x4 ring[kGruRing][3];
 #pragma unroll
-        for (int rb = 0; rb < NB; rb++) {
+    for (int i = 0; i < kGruRing; i++)
 #pragma unroll
-            for (int i = 0; i < 4; i++) {
-                const uint32_t row = 16u * rb + 4u * (lane >> 4) + i;
-                if (row >= m) continue;
-                const float rg = sigmoid_f32(acc[0][rb][i] + br);
-                const float zg = sigmoid_f32(acc[1][rb][i] + bz);
-                const float ng = tanh_f32(acc[2][rb][i] + bin + rg * (acc[3][rb][i] + bhn));
-                const float out = (1.0f - zg) * ng + zg * hv[rb][i];
-                uint8_t *srow = p.st + (size_t)m_self[row] * p.srb;
-                if (p.s_bf16)
-                    ((uint16_t *)srow)[j] = f32_to_bf16_rne(out);
-                else
-                    ((float *)srow)[j] = out;
+        for (int g = 0; g < 3; g++) ring[i][g] = (w0 + min((uint32_t)i, S - 1u) * 192u)[g * 64 + lane];
+    for (uint32_t u = tid; u < tpad; u += NT) {
+        T.s_tw[u] = u < p.d_time ? p.tw[u] : 0.0f;
+        T.s_tb[u] = u < p.d_time ? p.tb[u] : 0.0f;
+    }
+    const uint32_t blocks = (count + 15u) / 16u;
+    const uint32_t mine = blockIdx.x < blocks ? (blocks - 1u - blockIdx.x) / T.stride + 1u : 0u;
+    for (uint32_t k0 = 0; k0 < mine;) {
+        // The row blocks left, in tiles of sizes as equal as can be.
+        const uint32_t left = mine - k0, tiles = (left + p.nbmax - 1u) / p.nbmax, nb = (left + tiles - 1u) / tiles;
+        T.b0 = blockIdx.x + k0 * T.stride;
+        const uint64_t last = ((uint64_t)T.b0 + (uint64_t)(nb - 1u) * T.stride) * 16u;   // first row of the last block
+        T.m = 16u * (nb - 1u) + (uint32_t)min((uint64_t)16u, count - last);
+        if (k0) __syncthreads();   // the tile before has been read
+        if (tid < T.m) {
+            T.m_row[tid] = ent[0];
+            T.m_self[tid] = (int32_t)ent[1];
+            T.m_t[tid] = (float)ent[3];
+            p.winner[ent[1]] = 0ull;
+        }
+        k0 += nb;
+        if (k0 < mine) ent = list_entry(k0);
+        __syncthreads();
+        switch (nb) {
+#define NLB_GRU_FILL(NB)                                                       \
+        case NB:                                                               \
+            if constexpr (SF == kSegAny) gru_fill_any<NT, NB>(p, T, first_eid);    \
+            else gru_fill<NT, NB, SF, EF>(p, T, first_eid);                        \
+            break;
+            NLB_GRU_FILL(1) NLB_GRU_FILL(2) NLB_GRU_FILL(3)
+#undef NLB_GRU_FILL
+        }
+        __syncthreads();
+        const uint32_t each = (nb + split - 1u) / split, rb0 = part * each;
+        if (!works || rb0 >= nb) continue;
+        const uint32_t mb = min(each, nb - rb0);
+        for (uint32_t ub = ub0; ub < units; ub += split > 1u ? units : kWaves) {
+            const bool again = split == 1u && ub + kWaves < units;
+            const u32x4 *wp = p.wpack + (size_t)ub * S * 192u;
+            const u32x4 *wnext = again ? wp + (size_t)kWaves * S * 192u : w0;
+            const bool more = again || k0 < mine;
+            switch (mb) {
+#define NLB_GRU_UNITS(NB) \
+            case NB: gru_units<NB, SF, EF>(p, T, ring, wp, wnext, more, ub, rb0); break;
+                NLB_GRU_UNITS(1) NLB_GRU_UNITS(2) NLB_GRU_UNITS(3)
+#undef NLB_GRU_UNITS
             }
         }
     }
@@ -1363,13 +1492,11 @@ __global__ __launch_bounds__(kRnnThreads) void rnn_clear(unsigned long long *a, 
         a[i] = 0ull;
 }
 
-// LDS layout of a tile of `rows` pair rows; returns its size in bytes.
-uint32_t gru_layout(GruParams &p, uint32_t rows) {
-    p.rows = rows;
-    p.off_xl = align16(p.meta + rows * p.xs * 2u);
-    p.off_h = align16(p.off_xl + (p.lo_end > p.lo_begin ? rows * p.ls * 2u : 0u));
-    p.off_hl = align16(p.off_h + rows * p.hs * 2u);
-    return p.off_hl + (p.h_lo ? rows * p.hs * 2u : 0u);
+// LDS layout of a tile of nb 16-row blocks; returns its size in bytes.
+uint32_t gru_layout(GruParams &p, uint32_t nb) {
+    p.nbmax = nb;
+    p.off_xl = align16(p.meta + 16u * nb * p.xs * 2u);
+    return p.off_xl + (p.ls ? 16u * nb * p.ls * 2u : 0u);
 }
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -1537,12 +1664,11 @@ static int rnn_update(nlb_table *h, const int32_t *src, const int32_t *dst, cons
     p.lo_begin = lo_s ? 0 : (lo_t ? p.kd : (lo_e ? p.off_e : 0));
     p.lo_end = lo_e ? p.kx : (lo_t ? p.off_e : (lo_s ? p.kd : 0));
     p.h_lo = lo_s;
-    p.xs = p.kx + 8;
-    p.ls = (p.lo_end - p.lo_begin) + 8;
-    p.hs = p.kd + 8;
-    p.gx_m = nlb_div_magic(p.kx / 8);
+    const uint32_t lo_cols = p.lo_end - p.lo_begin + (p.h_lo ? p.kd : 0u);
+    p.xs = p.kx + p.kd + 8;
+    p.ls = lo_cols ? lo_cols + 8 : 0;
     p.gh_m = nlb_div_magic(p.kd / 8);
-    p.gt_m = p.off_e > p.kd ? nlb_div_magic((p.off_e - p.kd) / 8) : 0;
+    p.gt_m = p.off_e > p.kd ? nlb_div_magic((p.off_e - p.kd) / 4) : 0;
     p.ge_m = p.kx > p.off_e ? nlb_div_magic((p.kx - p.off_e) / 8) : 0;
     p.s_kind = piece_kind(p.srb, status, p.s_bf16);
     p.e_kind = h->efeat ? piece_kind(h->erb, h->efeat, p.e_bf16) : -1;
@@ -1553,11 +1679,7 @@ static int rnn_update(nlb_table *h, const int32_t *src, const int32_t *dst, cons
     p.b_hh = wts->b_hh;
 
     // Weight-stationary form when its weight fragments fit the registers and
-    // its two tile buffers the LDS; else tiles of 16 * nb listed rows: as
-    // large as the LDS budget of two workgroups per CU allows, smaller when
-    // the batch would give fewer than kGruTargetTiles tiles (counting all 2n
-    // pair rows; the winners are fewer); a 16-row tile may use a workgroup's
-    // whole LDS.
+    // its two tile buffers the LDS; else the tiled one (rnn_gru).
     const uint64_t pairs = 2ull * n;
     const uint32_t kh = p.kd / 32;
     // Forms whose registers fit without spills: bf16 rows of a width that is
@@ -1566,26 +1688,37 @@ static int rnn_update(nlb_table *h, const int32_t *src, const int32_t *dst, cons
     const int ws_mode = p.s_kind == kF32Vec ? kWsF32 : (p.d % 32 == 0 ? kWsBf16Dma : kWsBf16);
     bool ws = (p.s_kind == kBf16Vec || p.s_kind == kF32Vec) && kh <= (ws_mode == kWsBf16Dma ? 4u : 2u) &&
               p.kx / 32 + kh <= (uint32_t)kWsSteps && p.d_time > 0 && (p.kx == p.off_e || p.e_kind >= 0);
-    uint32_t lds = 0, nb = 4;
+    uint32_t lds = 0;
     int cus = 0;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, h->device) != hipSuccess || cus < 1)
+        return NLB_EDEVICE;
     if (ws) {
         // static LDS: tile buffers, row-list slots, link times, biases; dynamic: T-enc w | b
         const uint32_t fixed = kh == 1 ? WsLayout<1>::fixed : kh == 2 ? WsLayout<2>::fixed
                              : kh == 3 ? WsLayout<3>::fixed : WsLayout<4>::fixed;
         lds = 8u * pad32(p.d_time);
-        ws = fixed + lds <= kGruLdsMax &&
-             hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, h->device) == hipSuccess && cus > 0;
+        ws = fixed + lds <= kGruLdsMax;
         for (uint32_t st = p.lo_begin / 32; st < p.lo_end / 32; st++) p.ws_lomask |= 1u << st;
     }
+    const uint64_t blocks = (pairs + 15) / 16;   // at most (the winners are fewer)
+    uint64_t groups = 0;
+    uint32_t nt = p.d <= 64 && blocks > 4u * (uint64_t)cus ? 256 : 512;
     if (!ws) {
-        while (nb > 1 && pairs < (uint64_t)kGruTargetTiles * 16u * nb) nb /= 2;
-        for (;; nb /= 2) {
-            GruParams trial = p;
-            lds = gru_layout(trial, 16u * nb);
-            if (lds <= (nb == 1 ? kGruLdsMax : kGruLdsBudget)) break;
-            if (nb == 1) return NLB_EINVAL;   // one 16-row tile does not fit the LDS
+        // One workgroup of 512 threads per CU; two of 256 for statuses that
+        // give eight wavefronts no unit block each, in batches of several tiles
+        // per workgroup, where one's row reads then run beside the other's
+        // products (20 000 links, bf16 statuses of 34: 64.6 -> 61.3 us; one
+        // tile each, 5000 links, fp32 statuses of 50: 28.1 against 28.7).
+        // Tiles of as many row blocks as a workgroup can have (up to
+        // kGruBlocks) and its LDS holds.
+        for (;; nt = 512u) {
+            groups = nt == 256u ? 2u * (uint64_t)cus : (uint64_t)cus;
+            uint32_t nb = (uint32_t)std::min<uint64_t>(kGruBlocks, (blocks + groups - 1) / groups);
+            const uint32_t most = nt == 256u ? kGruLdsMax / 2u : kGruLdsMax;
+            while (nb && (lds = gru_layout(p, nb)) > most) nb--;
+            if (nb) break;
+            if (nt == 512u) return NLB_EINVAL;   // one 16-row block does not fit the LDS
         }
-        gru_layout(p, 16u * nb);
     }
 
     // packed weight fragments: kd / 16 unit blocks x (kx + kd) / 32 k-steps x 3 gates, 1 KB each
@@ -1626,7 +1759,7 @@ static int rnn_update(nlb_table *h, const int32_t *src, const int32_t *dst, cons
     // 23.3), else what the alignment allows.  (The staged rows start 256-byte
     // aligned.)
     const bool a4 = p.srb % 4 == 0 && (uintptr_t)status % 4 == 0;
-    SelectParams sp = {src, dst, n, h->num_nodes, wk.winner, list, count, p.st, wk.stage, p.srb,
+    SelectParams sp = {src, dst, t, n, h->num_nodes, wk.winner, list, count, p.st, wk.stage, p.srb,
                        a4 ? (p.srb >= 16 ? 16u : 4u) : 2u, 0, 0};
     sp.upr = (p.srb + sp.w - 1) / sp.w;
     sp.upr_m = nlb_div_magic(sp.upr);
@@ -1656,18 +1789,25 @@ static int rnn_update(nlb_table *h, const int32_t *src, const int32_t *dst, cons
         if (hipLaunchKernel(kern, grid, dim3(128u * kh), args, lds, (hipStream_t)stream) != hipSuccess)
             return NLB_EDEVICE;
     } else {
-        const void *kern = nb == 4 ? (const void *)rnn_gru<4>
-                         : nb == 2 ? (const void *)rnn_gru<2> : (const void *)rnn_gru<1>;
+        const int sf = seg_form(p.d, p.srb, status, p.s_bf16);
+        const int ef = p.kx > p.off_e ? seg_form(p.e_dim, p.erb, p.efeat, p.e_bf16) : kSegNone;
+        const void *kern = nullptr;
+        switch (sf == kSegAny || ef == kSegAny ? -1 : sf * 4 + ef) {
+#define NLB_GRU_CASE(SF, EF) \
+        case SF * 4 + EF: kern = nt == 256u ? (const void *)rnn_gru<256, SF, EF> : (const void *)rnn_gru<512, SF, EF>; break;
+        NLB_GRU_CASE(kSegBf16, kSegNone) NLB_GRU_CASE(kSegBf16, kSegBf16) NLB_GRU_CASE(kSegBf16, kSegF32)
+        NLB_GRU_CASE(kSegF32, kSegNone) NLB_GRU_CASE(kSegF32, kSegBf16) NLB_GRU_CASE(kSegF32, kSegF32)
+#undef NLB_GRU_CASE
+        default:
+            kern = nt == 256u ? (const void *)rnn_gru<256, kSegAny, kSegNone> : (const void *)rnn_gru<512, kSegAny, kSegNone>;
+        }
         if (lds > 64u * 1024u &&
             hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kGruLdsMax) != hipSuccess)
             return NLB_EDEVICE;
-        const dim3 grid((unsigned)((pairs + 16u * nb - 1) / (16u * nb)));
-        if (nb == 4)
-            hipLaunchKernelGGL(rnn_gru<4>, grid, dim3(kRnnThreads), lds, (hipStream_t)stream, p);
-        else if (nb == 2)
-            hipLaunchKernelGGL(rnn_gru<2>, grid, dim3(kRnnThreads), lds, (hipStream_t)stream, p);
-        else
-            hipLaunchKernelGGL(rnn_gru<1>, grid, dim3(kRnnThreads), lds, (hipStream_t)stream, p);
+        const dim3 grid((unsigned)std::min<uint64_t>(blocks, groups));
+        void *args[] = {&p};
+        if (hipLaunchKernel(kern, grid, dim3(nt), args, lds, (hipStream_t)stream) != hipSuccess)
+            return NLB_EDEVICE;
     }
     h->rnn_form = ws ? NLB_RNN_FORM_WEIGHT_STATIONARY : NLB_RNN_FORM_TILED;
     if (hipGetLastError() != hipSuccess) return NLB_EDEVICE;
