@@ -86,15 +86,14 @@ __device__ __forceinline__ bool link_ok(const InsertParams &p, int32_t u, int32_
 }
 
 // Pass 1.  Each link validates itself and turns into two offer words that
-// go to their slots with a 64-bit atomic maximum.  For large batches a
-// workgroup takes kResolveLinks consecutive links and first merges their
-// offers per slot in an LDS hash table (open addressing on the key word's
-// byte offset, 64-bit LDS atomics), so a slot that many of its offers hit --
-// the slots of a popular node -- costs one global atomic per workgroup
-// instead of one per offer; the maximum is associative, so the result is the
-// same.  Small batches skip the merge: they have few workgroups and little
-// same-slot traffic, and the plain atomics finish sooner.  The merge table
-// is merge_max of nlb_internal.h.
+// go to their slots with a 64-bit atomic maximum.  In all but small batches a
+// workgroup first merges its links' offers per slot in an LDS hash table (open
+// addressing on the key word's byte offset, 64-bit LDS atomics; merge_max of
+// nlb_internal.h), so a slot that many of its offers hit -- the slots of a
+// popular node -- costs one global atomic per workgroup instead of one per
+// offer; the maximum is associative, so the result is the same.  Small batches
+// skip the merge: they have little same-slot traffic, and the plain atomics
+// finish sooner.
 
 // Validation of link i (ranges; timestamps non-decreasing inside the batch
 // and against the last timestamp of the previous batch) and its two offers.
@@ -146,46 +145,33 @@ __global__ __launch_bounds__(kInsertThreads) void insert_resolve(InsertParams p)
     atomicMax((unsigned long long *)(p.blocks + ov), (unsigned long long)wv);
 }
 
-__global__ __launch_bounds__(kMergeThreads) void insert_resolve_merged(InsertParams p) {
-    __shared__ unsigned long long merge_off[kMergeEntries];
-    __shared__ unsigned long long merge_word[kMergeEntries];
-    for (int k = threadIdx.x; k < kMergeEntries; k += kMergeThreads) {
+template <int T>
+__global__ __launch_bounds__(T) void insert_resolve_merged(InsertParams p) {
+    __shared__ unsigned long long merge_off[kMergeEntries<T>];
+    __shared__ unsigned long long merge_word[kMergeEntries<T>];
+    // The thread's link is loaded (past the batch: the last one again, unused)
+    // while the table is cleared.
+    const uint32_t i = blockIdx.x * T + threadIdx.x, il = min(i, p.n - 1u);
+    const int32_t u = p.src[il], v = p.dst[il];
+    const uint32_t t = p.t[il], pt = prev_time(p, il);
+    const BatchPos bp = batch_pos(p, kWordLinks);
+    for (int k = threadIdx.x; k < kMergeEntries<T>; k += T) {
         merge_off[k] = 0ull;
         merge_word[k] = 0ull;
     }
     __syncthreads();
-    const BatchPos bp = batch_pos(p, kWordLinks);
     record_batch(p, bp);
     if (!bp.ok) {
         if (blockIdx.x == 0 && threadIdx.x == 0) atomicOr(p.status, kStatusRange);
         return;   // uniform over the grid: no workgroup waits at a later barrier
     }
-    // All of a thread's links are loaded (a link past the batch re-reads
-    // the last one, unused) before any is merged.
-    constexpr int RR = kResolveLinks / kMergeThreads;
-    const uint32_t first = blockIdx.x * kResolveLinks;
-    int32_t uu[RR], vv[RR];
-    uint32_t tt[RR], pt[RR];
-#pragma unroll
-    for (int r = 0; r < RR; r++) {
-        const uint32_t i = min(first + r * kMergeThreads + threadIdx.x, p.n - 1u);
-        uu[r] = p.src[i];
-        vv[r] = p.dst[i];
-        tt[r] = p.t[i];
-        pt[r] = prev_time(p, i);
-    }
-#pragma unroll
-    for (int r = 0; r < RR; r++) {
-        const uint32_t i = first + r * kMergeThreads + threadIdx.x;
-        if (i >= p.n) break;
-        uint64_t ou, wu, ov, wv;
-        if (link_offers_of(p, bp, i, uu[r], vv[r], tt[r], pt[r], ou, wu, ov, wv)) {
-            merge_max(merge_off, merge_word, ou, wu);
-            merge_max(merge_off, merge_word, ov, wv);
-        }
+    uint64_t ou, wu, ov, wv;
+    if (i < p.n && link_offers_of(p, bp, i, u, v, t, pt, ou, wu, ov, wv)) {
+        merge_max<T>(merge_off, merge_word, ou, wu);
+        merge_max<T>(merge_off, merge_word, ov, wv);
     }
     __syncthreads();
-    for (int k = threadIdx.x; k < kMergeEntries; k += kMergeThreads) {
+    for (int k = threadIdx.x; k < kMergeEntries<T>; k += T) {
         const unsigned long long tag = merge_off[k];
         if (tag) atomicMax((unsigned long long *)(p.blocks + (tag - 1)), merge_word[k]);
     }
@@ -762,9 +748,10 @@ int nlb_insert_batch(nlb_table *h, const int32_t *src, const int32_t *dst, const
     p.key_mode = (uint32_t)h->key_mode;
     p.status = h->status;
     const hipStream_t st = (hipStream_t)stream;
-    if (n >= kMergeMinBatch)
-        hipLaunchKernelGGL(insert_resolve_merged, dim3((n + kResolveLinks - 1) / kResolveLinks),
-                           dim3(kMergeThreads), 0, st, p);
+    if (n >= kMergeLarge)
+        hipLaunchKernelGGL(insert_resolve_merged<1024>, dim3((n + 1023) / 1024), dim3(1024), 0, st, p);
+    else if (n >= kMergeInsert)
+        hipLaunchKernelGGL(insert_resolve_merged<512>, dim3((n + 511) / 512), dim3(512), 0, st, p);
     else
         hipLaunchKernelGGL(insert_resolve, dim3((n + kInsertThreads - 1) / kInsertThreads),
                            dim3(kInsertThreads), 0, st, p);

@@ -154,26 +154,40 @@ __device__ __forceinline__ SlotLds read_slot(const uint8_t *blocks, uint32_t blo
 // ---------------------------------------------------------------- LDS max-merge
 // Open-addressing LDS table that merges 64-bit maxima per global address
 // (byte offset `off`): merge_max records max(word) for off, so one global
-// atomicMax per distinct address can replace many.  kMergeEntries entries
-// hold up to half as many distinct addresses.
-constexpr int kResolveLinks = 1024;               // links merged per workgroup (two addresses each)
-constexpr int kMergeThreads = 1024;               // threads of a merging workgroup (one link each)
-constexpr int kMergeBits = 12;                    // 2 * kResolveLinks addresses: load <= 1/2
-constexpr int kMergeEntries = 1 << kMergeBits;
-constexpr uint32_t kMergeMinBatch = 65536;        // batches from this size merge in LDS
-static_assert(kMergeEntries >= 4 * kResolveLinks, "merge table size");
+// atomicMax per distinct address can replace many.
+//
+// A merging workgroup of T threads takes T links, one per thread.  What this
+// saves: atomics on one address follow each other about 12 ns apart, and a
+// popular node's slot or word takes one per link that has it (50 000 links with
+// power-law endpoints: the hottest node kept the launch waiting for 100 us).
+// What it costs: the table's clearing and probing, about 2 us.
+// Updates of the statuses merge from 1024 links (1 000 000 nodes, popularity
+// exponent 1.05: 10 000 links 49.4 us plain, 31.6 merged, 50 000 links 142.6 and
+// 43.6; exponent 0.5, 10 000 links: 29.3 and 31.1), insertions, whose offers
+// spread over a node's slots, from 32768 (exponent 1.05: 10 000 links 11.3 us
+// plain, 10.2 merged, 30 000 links 23.6 and 13.2; exponent 0.5, 10 000 links 7.4
+// and 9.3, 30 000 links 9.1 and 11.7).  Larger batches take larger workgroups,
+// which send a popular address's maximum fewer times (insertion of 60 000 links,
+// exponent 1.05: 28.9 us with 256 threads, 19.4 with 512, 15.4 with 1024).
+constexpr uint32_t kMergeUpdate = 1024, kMergeInsert = 32768;   // links from which batches merge
+constexpr uint32_t kMergeMid = 16384, kMergeLarge = 65536;      // links from which workgroups have 512, 1024 threads
+// Table entries, for up to two addresses per link: load <= 1/2.
+template <int T> constexpr int kMergeBits = 1 + kMergeBits<T / 2>;
+template <> constexpr int kMergeBits<1> = 2;
+template <int T> constexpr int kMergeEntries = 1 << kMergeBits<T>;
 
+template <int T>
 __device__ __forceinline__ void merge_max(unsigned long long *merge_off, unsigned long long *merge_word,
                                           uint64_t off, uint64_t word) {
     const unsigned long long tag = off + 1;  // 0 marks a free entry
-    uint32_t h = (uint32_t)(((off >> 3) * kGolden) >> (64 - kMergeBits));
+    uint32_t h = (uint32_t)(((off >> 3) * kGolden) >> (64 - kMergeBits<T>));
     for (;;) {
         const unsigned long long prev = atomicCAS(&merge_off[h], 0ull, tag);
         if (prev == 0ull || prev == tag) {
             atomicMax(&merge_word[h], (unsigned long long)word);
             return;
         }
-        h = (h + 1) & (kMergeEntries - 1);
+        h = (h + 1) & (kMergeEntries<T> - 1);
     }
 }
 

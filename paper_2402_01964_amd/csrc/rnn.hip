@@ -15,8 +15,8 @@
 //   resolve  each endpoint offers the code 2i + k + 1 of its pair row (link
 //            i, endpoint k) to winner[node] with a 64-bit atomic maximum (the
 //            array is all zero between calls: the gru pass clears the words
-//            it has used).  Large batches merge their offers per node in LDS
-//            first (merge_max), as the table insertion does.  Workgroups
+//            it has used).  All but small batches merge their offers per node
+//            in LDS first (merge_max), as the table insertion does.  Workgroups
 //            beside them repack the weights into matrix-operand fragments, so
 //            that the gru pass reads each with one contiguous 1 KB load.
 //   select   each pair row checks whether it won; the winners are appended
@@ -124,41 +124,31 @@ __global__ __launch_bounds__(kRnnThreads) void rnn_resolve(ResolveParams p) {
     atomicMax(&p.winner[v], (unsigned long long)(2ull * i + 2));
 }
 
-__global__ __launch_bounds__(kMergeThreads) void rnn_resolve_merged(ResolveParams p) {
-    if (blockIdx.x >= p.link_blocks) return pack_weights<kMergeThreads>(p);
-    __shared__ unsigned long long merge_off[kMergeEntries];
-    __shared__ unsigned long long merge_word[kMergeEntries];
-    for (int k = threadIdx.x; k < kMergeEntries; k += kMergeThreads) {
+template <int T>
+__global__ __launch_bounds__(T) void rnn_resolve_merged(ResolveParams p) {
+    if (blockIdx.x >= p.link_blocks) return pack_weights<T>(p);
+    __shared__ unsigned long long merge_off[kMergeEntries<T>];
+    __shared__ unsigned long long merge_word[kMergeEntries<T>];
+    // The thread's link is loaded (past the batch: the last one again, unused)
+    // while the table is cleared.
+    const uint32_t i = blockIdx.x * T + threadIdx.x, il = min(i, p.n - 1u);
+    const int32_t u = p.src[il], v = p.dst[il];
+    for (int k = threadIdx.x; k < kMergeEntries<T>; k += T) {
         merge_off[k] = 0ull;
         merge_word[k] = 0ull;
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0) *p.count = 0;
+    if (i == 0) *p.count = 0;
     __syncthreads();
-    // All of a thread's links are loaded (a link past the batch re-reads
-    // the last one, unused) before any is merged.
-    constexpr int RR = kResolveLinks / kMergeThreads;
-    const uint32_t first = blockIdx.x * kResolveLinks;
-    int32_t uu[RR], vv[RR];
-#pragma unroll
-    for (int r = 0; r < RR; r++) {
-        const uint32_t i = min(first + r * kMergeThreads + threadIdx.x, p.n - 1u);
-        uu[r] = p.src[i];
-        vv[r] = p.dst[i];
-    }
-#pragma unroll
-    for (int r = 0; r < RR; r++) {
-        const uint32_t i = first + r * kMergeThreads + threadIdx.x;
-        if (i >= p.n) break;
-        const int32_t u = uu[r], v = vv[r];
-        if (!endpoints_ok(u, v, p.num_nodes)) {
+    if (i < p.n) {
+        if (endpoints_ok(u, v, p.num_nodes)) {
+            merge_max<T>(merge_off, merge_word, 8ull * (uint32_t)u, 2ull * i + 1);
+            merge_max<T>(merge_off, merge_word, 8ull * (uint32_t)v, 2ull * i + 2);
+        } else {
             atomicOr(p.status, kStatusRange);
-            continue;
         }
-        merge_max(merge_off, merge_word, 8ull * (uint32_t)u, 2ull * i + 1);
-        merge_max(merge_off, merge_word, 8ull * (uint32_t)v, 2ull * i + 2);
     }
     __syncthreads();
-    for (int k = threadIdx.x; k < kMergeEntries; k += kMergeThreads) {
+    for (int k = threadIdx.x; k < kMergeEntries<T>; k += T) {
         const unsigned long long tag = merge_off[k];
         if (tag) atomicMax(&p.winner[(tag - 1) >> 3], merge_word[k]);
     }
@@ -1610,7 +1600,7 @@ int scratch_work(nlb_table *h, uint64_t pairs, uint32_t srb, size_t wpack_bytes,
 
 // Both entry points: argument checks, the GRU form and tile shape, the
 // working memory (the table's own, grown on demand, or the static array),
-// then the four launches.
+// then the three launches.
 static int rnn_update(nlb_table *h, const int32_t *src, const int32_t *dst, const uint32_t *t, uint32_t n,
                       uint64_t first_eid, const nlb_gru_weights *wts, void *status, void *stream,
                       bool use_scratch) {
@@ -1745,15 +1735,17 @@ static int rnn_update(nlb_table *h, const int32_t *src, const int32_t *dst, cons
                         p.w_ih, p.w_hh, (u32x4 *)wk.wpack, p.d, p.kx, p.kd, p.kx / 32, (p.kx + p.kd) / 32,
                         (uint32_t)(wpack_bytes / 16)};
     // (the weight pack by workgroups of its own: one piece per thread)
-    if (n >= kMergeMinBatch) {
-        rp.link_blocks = (n + kResolveLinks - 1) / kResolveLinks;
-        hipLaunchKernelGGL(rnn_resolve_merged, dim3(rp.link_blocks + (rp.pieces + kMergeThreads - 1) / kMergeThreads),
-                           dim3(kMergeThreads), 0, (hipStream_t)stream, rp);
-    } else {
-        rp.link_blocks = (n + kRnnThreads - 1) / kRnnThreads;
-        hipLaunchKernelGGL(rnn_resolve, dim3(rp.link_blocks + (rp.pieces + kRnnThreads - 1) / kRnnThreads),
-                           dim3(kRnnThreads), 0, (hipStream_t)stream, rp);
-    }
+    const uint32_t rt = n >= kMergeLarge ? 1024u : n >= kMergeMid ? 512u : 256u;
+    rp.link_blocks = (n + rt - 1u) / rt;
+    const dim3 rgrid(rp.link_blocks + (rp.pieces + rt - 1u) / rt);
+    if (n >= kMergeLarge)
+        hipLaunchKernelGGL(rnn_resolve_merged<1024>, rgrid, dim3(rt), 0, (hipStream_t)stream, rp);
+    else if (n >= kMergeMid)
+        hipLaunchKernelGGL(rnn_resolve_merged<512>, rgrid, dim3(rt), 0, (hipStream_t)stream, rp);
+    else if (n >= kMergeUpdate)
+        hipLaunchKernelGGL(rnn_resolve_merged<256>, rgrid, dim3(rt), 0, (hipStream_t)stream, rp);
+    else
+        hipLaunchKernelGGL(rnn_resolve, rgrid, dim3(rt), 0, (hipStream_t)stream, rp);
     // Copy unit of the staged rows: 16 bytes at 4-byte alignment (rows of 252
     // bytes in 4-byte units: the whole update of 556 links 27.9 us, against
     // 23.3), else what the alignment allows.  (The staged rows start 256-byte
