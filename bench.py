@@ -143,12 +143,17 @@ def aggregate_kernel(w, queries, cus, heads=1):
     """The eq. (4) kernel a launch of `queries` takes on this workload's
     shapes (the library's own choice, restated for the record): with one or
     two heads, the packed form for tables of at most 16 slots when its query
-    groups hold at least 8 queries, else the per-query form; more heads take
-    the tiled form."""
+    groups hold at least 8 queries, else the grouped form for link rows of 161
+    to 192 values without node rows (two queries per wavefront, or rows that
+    are not 16-byte aligned), else the per-query form; more heads take the
+    tiled form."""
     if heads > 2:
         return "aggregate_fused"
     gq = min(16, max(1, -(-queries // (cus * 8))))
-    return "aggregate_packed" if w.s <= 16 and gq >= 8 else "aggregate_rows"
+    if w.s <= 16 and gq >= 8:
+        return "aggregate_packed"
+    wide = not w.node_dim and 160 < w.edge_dim <= 192
+    return "aggregate_groups" if wide and (gq >= 2 or w.row_bytes("edge") % 16) else "aggregate_rows"
 
 
 def hop2_bytes(w, hop1_valid, queries):

@@ -2361,9 +2361,20 @@ extern "C" int nlb_aggregate(nlb_table *h, const int32_t *node, const uint32_t *
         // are large enough for packing to fill blocks (small launches are
         // bound by their per-group steps).
         const bool packed = h->s <= kPackMaxS && r.gq >= kPackMinGroup && heads <= 2;
-        // One or two heads: the packed or the per-query kernel; more heads take
-        // the tiled kernel.
-        const bool rows_ok = heads <= 2;
+        // One or two heads: the packed, the grouped or the per-query kernel;
+        // more heads take the tiled kernel.  Wide link rows without node rows
+        // (161 to 192 values) leave most of a per-query block's time to its
+        // empty rows: aggregate_groups is faster as soon as a wavefront has two
+        // queries (20 slots, fp32 rows of 172 values: 4500 queries 32.9 us per
+        // query, 27.4 grouped, 12 000 queries 57.6 and 45.3, 1800 queries 18.4
+        // and 18.8; 10 slots, 12 000 queries 38.1 and 29.7), and at any size for
+        // rows at 4-byte alignment, which it reads in 16-byte units (bf16 rows of
+        // 186 values: 1800 queries 19.4 and 16.3, 12 000 queries 62.8 and 38.2).
+        // Narrower link rows, or node rows beside them, stay with the per-query
+        // kernel (rows of 100 values, 1800 queries: 14.7 and 18.5).
+        const bool grouped = !packed && h->s <= kGroupMaxS && nks == 0 && eks == 6 &&
+                             (ekind == kBf16Word || r.gq >= 2);
+        const bool rows_ok = heads <= 2 && !grouped;
 #define NLB_ROWS_SHAPE(A, B, C, NK, EK)                                                              \
     if (!kern && rows_ok && nkind >= 0 && ekind >= 0 && nks == A && eks == B && tks == C && (A == 0 || nkind == NK) &&            \
         (B == 0 || ekind == EK)) {                                                                    \

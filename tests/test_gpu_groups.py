@@ -54,6 +54,22 @@ def _off16(t):
 
 @pytest.mark.parametrize("case", CASES, ids=_ids)
 def test_any_width_aggregation_matches_oracle(case):
+    _check_against_oracle(case, _off16)
+
+
+# Wide link rows without node rows, at 16-byte alignment: the per-query kernel
+# or this one by the number of queries (none, or two and more, per wavefront).
+WIDE = [(0, "f32", 172, "f32", 100, 20, 1), (0, "f32", 164, "f32", 100, 10, 2),
+        (0, "f32", 186, "bf16", 100, 20, 2), (0, "f32", 172, "f32", 100, 64, 1),
+        (0, "f32", 172, "f32", 100, 65, 1)]
+
+
+@pytest.mark.parametrize("case", WIDE, ids=_ids)
+def test_wide_link_rows_match_oracle(case):
+    _check_against_oracle(case, lambda t: t)
+
+
+def _check_against_oracle(case, place):
     import paper_2402_01964_amd as nlb
     dn, nt, de, et, d_time, s, heads = case
     base = synth.workload(1)
@@ -67,8 +83,8 @@ def test_any_width_aggregation_matches_oracle(case):
     fw, fb = synth.time_params(w) if d_time else (np.zeros(0, np.float32),) * 2
     g = nlb.Table(w.num_nodes, s, w.alpha, w.table_seed,
                   time_w=to_dev(fw) if d_time else None, time_b=to_dev(fb) if d_time else None,
-                  edge_feat=_off16(feat_to_dev(ef, et)) if ef is not None else None,
-                  node_feat=_off16(feat_to_dev(nf, nt)) if nf is not None else None)
+                  edge_feat=place(feat_to_dev(ef, et)) if ef is not None else None,
+                  node_feat=place(feat_to_dev(nf, nt)) if nf is not None else None)
     o = oracle.Oracle(w.num_nodes, s, w.alpha, w.table_seed)
     g.insert(to_dev(src), to_dev(dst), to_dev(t))
     o.insert(src, dst, t)
