@@ -750,9 +750,13 @@ __device__ __forceinline__ void gru_units(const GruParams &p, const GruTile &T, 
     const std::false_type no;
     const std::integral_constant<int, 2> x;
     const std::integral_constant<int, 3> h;
+    // X's steps 0 .. lb - 1, lb .. le - 1 (those with a lo plane), le .. kxm - 1.
+    // lb is 0 with fp32 statuses, le is kxm with fp32 link rows, and with fp32
+    // statuses and no link rows.  (bf16 statuses without link rows or time
+    // encoding have no lo plane: lb = le = 0.)
     if constexpr (SF != kSegF32) segment(no, x, 0u, lb, 0u);
     segment(lo, x, lb, le, 0u);
-    if constexpr (EF == kSegBf16 || SF == kSegAny) segment(no, x, le, kxm, 0u);
+    if constexpr (EF == kSegBf16 || (EF == kSegNone && SF != kSegF32)) segment(no, x, le, kxm, 0u);
     if (SF == kSegF32 || (SF == kSegAny && p.h_lo))
         segment(lo, h, kxm, S, le - lb);
     else

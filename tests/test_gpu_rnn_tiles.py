@@ -37,8 +37,29 @@ CASES = [
 ]
 
 
-@pytest.mark.parametrize("case", CASES, ids=lambda c: f"d{c[0]}{c[1]}-t{c[2]}-e{c[3]}{c[4]}-n{c[5]}")
+def _ids(c):
+    return f"d{c[0]}{c[1]}-t{c[2]}-e{c[3]}{c[4]}-n{c[5]}"
+
+
+@pytest.mark.parametrize("case", CASES, ids=_ids)
 def test_update_tiles(case):
+    _check_tiles(case)
+
+
+# bf16 statuses without a time encoding: no column of the input has a second
+# bf16 term (no link rows, or bf16 ones), or the link rows' columns alone.
+# One, two, four, five and seven k-steps of the status; a few rows and more
+# than one tile per workgroup.
+BARE = [(d, "bf16", 0, e, et, n) for d, n in ((8, 3), (34, 2100), (64, 6146), (128, 2049), (160, 40), (200, 2050))
+        for e, et in ((0, "f32"), (10, "bf16"), (7, "f32"), (4, "bf16"), (3, "f32"))]
+
+
+@pytest.mark.parametrize("case", BARE, ids=_ids)
+def test_update_tiles_without_time_encoding(case):
+    _check_tiles(case)
+
+
+def _check_tiles(case):
     d, dtype, d_time, e_dim, e_dtype, n = case
     rng = np.random.default_rng(n + d)
     N = 2 * n + 5
