@@ -202,14 +202,18 @@ __device__ __forceinline__ void stage_rows(const SelectParams &p, const u32x4 *r
     }
 }
 
-constexpr uint64_t kSelectSmall = 128 * 256;   // pair rows up to which select's workgroups have 256 threads
+constexpr uint64_t kSelectSmall = 256 * 256;   // pair rows up to which select's workgroups have 256 threads
 
 // A workgroup checks T consecutive pair rows, one per thread, collects its
 // winners in LDS (one LDS atomic per wavefront) and appends them to the list
 // with a single global atomic.  All workgroups' atomics go to one word, which
-// takes them about 12 ns apart: 200 000 pair rows in workgroups of 256 threads
-// (782 atomics) took 16.0 us, of 512 13.0 and of 1024 11.3, so large batches use
-// 1024; small ones use 256, which spreads their rows over more CUs.
+// takes them about 12 ns apart, so large batches use workgroups of 1024 (782
+// atomics of 256-thread workgroups for 200 000 pair rows; the whole update, bf16
+// statuses of 128: 55.4 us with 256 threads, 49.1 with 1024).  Smaller ones use
+// 256: the winners' rows are staged by the workgroup that finds them, and 40
+// workgroups of 1024 leave most of the 256 CUs idle (40 000 pair rows, fp32
+// statuses of 100: 66.1 us with 1024 threads, 61.4 with 256; 80 000: 103.7 and
+// 102.8, with bf16 statuses of 128 and popular nodes 37.9 and 38.9).
 template <uint32_t T>
 __global__ __launch_bounds__(T) void rnn_select(SelectParams p) {
     __shared__ u32x4 rows[T];

@@ -18,14 +18,16 @@ pytestmark = pytest.mark.gpu
 
 # (status width, type, d_time, link width, type, links, nodes)
 CASES = [
-    (100, "f32", 100, 0, "f32", 16384, 9000),     # 32 768 pair rows: the most for 256-thread select
-    (100, "f32", 12, 0, "f32", 16385, 30000),     # one more
+    (100, "f32", 100, 0, "f32", 16384, 9000),     # merged by workgroups of 512 links from here on
+    (100, "f32", 12, 0, "f32", 16385, 30000),
     (50, "f32", 20, 6, "f32", 16385, 700),        # 8-byte units
     (33, "f32", 12, 5, "f32", 17001, 30000),      # 4-byte units
     (33, "bf16", 12, 6, "bf16", 17001, 30000),    # 2-byte units
     (128, "bf16", 100, 0, "f32", 65535, 40000),   # unmerged resolve, weight-stationary pass
     (128, "bf16", 100, 0, "f32", 65536, 500),     # merged resolve, few nodes
     (33, "bf16", 12, 6, "bf16", 257, 60),
+    (20, "f32", 12, 0, "f32", 32768, 40000),      # 65 536 pair rows: the most for 256-thread select
+    (20, "f32", 12, 0, "f32", 32769, 900),        # one more
 ]
 
 
