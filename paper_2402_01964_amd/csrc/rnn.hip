@@ -70,6 +70,7 @@ namespace {
 constexpr int kRnnThreads = 256;
 constexpr uint32_t kGruMetaRows = 1024;           // LDS bytes of the tile's row list (4 words per row)
 constexpr uint32_t kGruLdsMax = 160 * 1024;       // gfx950: LDS of one workgroup at most
+constexpr uint32_t kGruTargetTiles = 1024;        // tiles of rnn_gru_tiles wanted per launch (counted on 2n rows)
 
 struct ResolveParams {
     const int32_t *src;
@@ -875,6 +876,286 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
     }
 }
 
+// ---------------------------------------------------------------- one tile per workgroup
+// The tiled GRU pass with a workgroup of four wavefronts per tile of NB 16-row
+// blocks of the list (rnn_gru_tiles), three or four workgroups on a CU: the row
+// reads of one run beside the products of another, where rnn_gru's one or two
+// workgroups of 256 registers a lane have little beside them.  Wavefront w
+// computes unit blocks w, w + 4, ...; every tile reads all weights from L2, which
+// bounds it where rows are wide.  (Tiles of four blocks took 250 registers and
+// ran slower than tiles of two: 100 000 links, bf16 statuses of 144: 283 us for
+// the whole update, 231 with two.)
+//
+// acc[g'][rb] += A_rb (16 x 32 blocks of the LDS pair Ah/Al, row stride
+// `as`; the lo plane starts at column lo_b with its own stride `ls`)
+//              * W_g^T for the three gates, over the k-steps kb, kb + 32, ..
+// < ke; g' = g for the r and z gates and g' = NIDX for the n gate.  LO adds
+// the lo-plane products.  The weights come packed (rnn_resolve): wp points at
+// this lane's word of the fragment (k-step 0, gate 0) of the matrix and unit
+// block; fragment (k-step s, gate g) is 192 s + 64 g words on.
+template <int NB, bool LO, int NIDX>
+__device__ __forceinline__ void gate_seg(f32x4 (&acc)[4][NB], const __bf16 *Ah, const __bf16 *Al,
+                                         uint32_t as, uint32_t ls, uint32_t lo_b, const u32x4 *wp,
+                                         uint32_t kb, uint32_t ke, uint32_t lr, uint32_t lk) {
+    if (kb >= ke) return;
+    const uint32_t last = ke - 32;
+    bf16x8 r0[3], r1[3], r2[3];
+    auto load = [&](bf16x8 (&b)[3], uint32_t k) {
+#pragma unroll
+        for (int g = 0; g < 3; g++) b[g] = __builtin_bit_cast(bf16x8, wp[(k >> 5) * 192u + g * 64u]);
+    };
+    auto step = [&](const bf16x8 (&b)[3], uint32_t k0) {
+        bf16x8 a[NB], al[NB];
+#pragma unroll
+        for (int rb = 0; rb < NB; rb++) a[rb] = *(const bf16x8 *)(Ah + (16u * rb + lr) * as + k0 + lk);
+        if (LO) {
+#pragma unroll
+            for (int rb = 0; rb < NB; rb++)
+                al[rb] = *(const bf16x8 *)(Al + (16u * rb + lr) * ls + (k0 - lo_b) + lk);
+        }
+#pragma unroll
+        for (int rb = 0; rb < NB; rb++)
+#pragma unroll
+            for (int g = 0; g < 3; g++) {
+                const int gi = g == 2 ? NIDX : g;
+                acc[gi][rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[rb], b[g], acc[gi][rb], 0, 0, 0);
+            }
+        if (LO) {
+#pragma unroll
+            for (int rb = 0; rb < NB; rb++)
+#pragma unroll
+                for (int g = 0; g < 3; g++) {
+                    const int gi = g == 2 ? NIDX : g;
+                    acc[gi][rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al[rb], b[g], acc[gi][rb], 0, 0, 0);
+                }
+        }
+        // All LDS reads of the step first, then its products.
+        __builtin_amdgcn_sched_group_barrier(0x0100, LO ? 2 * NB : NB, 0);
+        __builtin_amdgcn_sched_group_barrier(0x0008, LO ? 6 * NB : 3 * NB, 0);
+    };
+    // Three-slot ring: the loads of step k + 64 are issued before the
+    // products of step k (the scheduling barriers keep them there).
+    // Prefetches past the segment re-read its last step (in bounds, unused).
+    load(r0, kb);
+    load(r1, kb + 32 < ke ? kb + 32 : last);
+    uint32_t k0 = kb;
+    for (; k0 + 64 < ke; k0 += 96) {
+        load(r2, k0 + 64);
+        __builtin_amdgcn_sched_barrier(0);
+        step(r0, k0);
+        load(r0, k0 + 96 < ke ? k0 + 96 : last);
+        __builtin_amdgcn_sched_barrier(0);
+        step(r1, k0 + 32);
+        load(r1, k0 + 128 < ke ? k0 + 128 : last);
+        __builtin_amdgcn_sched_barrier(0);
+        step(r2, k0 + 64);
+    }
+    if (k0 < ke) step(r0, k0);
+    if (k0 + 32 < ke) step(r1, k0 + 32);
+}
+
+
+// A tile's inputs; tile rows past T.m are zeros.  Rows in their piece forms
+// (nlb_pieces.h), all pieces of a thread (up to 8) requested before any is
+// stored; where status or link rows have none, both element by element.
+template <int NB>
+__device__ __forceinline__ void gru_tile_fill(const GruParams &p, const GruTile &T) {
+    constexpr uint32_t R = 16 * NB;
+    const uint64_t first_eid = first_eid_of(p);
+    __bf16 *Hh = T.hi + p.kx, *Hl = T.lo + (p.lo_end - p.lo_begin);
+    const uint32_t gh = p.kd / 8, ge = (p.kx - p.off_e) / 8, us = 2u * R * gh;
+    // Status rows: the first R r_self, the next R r_other.
+    auto status_row = [&](uint32_t jj) {
+        const uint32_t j = jj < R ? jj : jj - R, jm = j < T.m ? j : 0u;
+        return jj < R ? p.st + (size_t)T.m_self[jm] * p.srb : p.stage + ((size_t)16u * T.b0 + jm) * p.srb;
+    };
+    auto link_of = [&](uint32_t j) { return first_eid + (T.m_row[j < T.m ? j : 0u] >> 1); };
+    if (p.s_kind >= 0 && (p.e_kind >= 0 || ge == 0)) {
+        auto status_fill = [&](auto kind) {
+            constexpr int K = decltype(kind)::value;
+            fill_seg<K, 8, kRnnThreads>(us, gh, p.gh_m, p.d, status_row,
+                                        [&](uint32_t jj, uint32_t c0, const Piece8<K> &pc) {
+                const bool self = jj < R;
+                const uint32_t j = self ? jj : jj - R;
+                const bool ok = j < T.m;
+                __bf16 *hi = (self ? Hh : T.hi) + (size_t)j * p.xs + c0;
+                if constexpr (K == kF32Vec) {
+                    float v[8];
+                    piece_floats<K>(pc, p.d, c0, ok, v);
+                    store_split8(v, hi, (self ? Hl : T.lo) + (size_t)j * p.ls + c0);   // lo_begin == 0
+                } else {
+                    *(u32x4 *)hi = piece_bf16_bits<K>(pc, p.d, c0, ok);
+                }
+            });
+        };
+        if (p.s_kind == kF32Vec)
+            status_fill(std::integral_constant<int, kF32Vec>{});
+        else if (p.s_kind == kBf16Word)
+            status_fill(std::integral_constant<int, kBf16Word>{});
+        else
+            status_fill(std::integral_constant<int, kBf16Vec>{});
+        gru_encode<kRnnThreads, NB>(p, T);
+        if (ge) {
+            auto edge_fill = [&](auto kind) {
+                constexpr int K = decltype(kind)::value;
+                fill_seg<K, 8, kRnnThreads>(
+                    R * ge, ge, p.ge_m, p.e_dim,
+                    [&](uint32_t j) {
+                        const uint64_t e = link_of(j);
+                        return p.efeat + (size_t)(e < (uint64_t)p.edge_rows ? e : 0u) * p.erb;
+                    },
+                    [&](uint32_t j, uint32_t c0, const Piece8<K> &pc) {
+                        const bool ok = j < T.m && link_of(j) < (uint64_t)p.edge_rows;
+                        __bf16 *hi = T.hi + (size_t)j * p.xs + p.off_e + c0;
+                        if constexpr (K == kF32Vec) {
+                            float v[8];
+                            piece_floats<K>(pc, p.e_dim, c0, ok, v);
+                            store_split8(v, hi, T.lo + (size_t)j * p.ls + (p.off_e + c0 - p.lo_begin));
+                        } else {
+                            *(u32x4 *)hi = piece_bf16_bits<K>(pc, p.e_dim, c0, ok);
+                        }
+                    });
+            };
+            if (p.e_kind == kF32Vec)
+                edge_fill(std::integral_constant<int, kF32Vec>{});
+            else if (p.e_kind == kBf16Word)
+                edge_fill(std::integral_constant<int, kBf16Word>{});
+            else
+                edge_fill(std::integral_constant<int, kBf16Vec>{});
+        }
+        return;
+    }
+    gru_encode<kRnnThreads, NB>(p, T);
+    constexpr int F = 4 * NB;   // units of a thread in flight
+    const uint32_t ut = us + R * ge;
+    for (uint32_t base = threadIdx.x; base < ut; base += kRnnThreads * F) {
+        float v[F][8];
+#pragma unroll
+        for (int f = 0; f < F; f++) {
+            const uint32_t u = base + f * kRnnThreads;
+#pragma unroll
+            for (int i = 0; i < 8; i++) v[f][i] = 0.0f;
+            if (u < us) {
+                const uint32_t jj = nlb_div(u, p.gh_m), c = (u - jj * gh) * 8u;
+                if ((jj < R ? jj : jj - R) < T.m)
+                    load8(status_row(jj), p.d, p.s_bf16, jj < R ? p.s_vec : p.o_vec, c, v[f]);
+            } else if (u < ut) {
+                const uint32_t j = nlb_div(u - us, p.ge_m), c = (u - us - j * ge) * 8u;
+                const uint64_t e = link_of(j);
+                if (j < T.m && e < (uint64_t)p.edge_rows)
+                    load8(p.efeat + (size_t)e * p.erb, p.e_dim, p.e_bf16, p.e_vec, c, v[f]);
+            }
+        }
+#pragma unroll
+        for (int f = 0; f < F; f++) {
+            const uint32_t u = base + f * kRnnThreads;
+            if (u < us) {
+                const uint32_t jj = nlb_div(u, p.gh_m), c = (u - jj * gh) * 8u;
+                const bool self = jj < R;
+                const uint32_t j = self ? jj : jj - R;
+                __bf16 *hi = (self ? Hh : T.hi) + (size_t)j * p.xs + c;
+                if (p.h_lo)
+                    store_split8(v[f], hi, (self ? Hl : T.lo) + (size_t)j * p.ls + c);
+                else
+                    store_hi8(v[f], hi);
+            } else if (u < ut) {
+                const uint32_t j = nlb_div(u - us, p.ge_m), c = p.off_e + (u - us - j * ge) * 8u;
+                if (p.lo_end == p.kx)
+                    store_split8(v[f], T.hi + (size_t)j * p.xs + c, T.lo + (size_t)j * p.ls + (c - p.lo_begin));
+                else
+                    store_hi8(v[f], T.hi + (size_t)j * p.xs + c);
+            }
+        }
+    }
+}
+
+template <int NB>
+__global__ __launch_bounds__(kRnnThreads) void rnn_gru_tiles(GruParams p) {
+    constexpr uint32_t R = 16 * NB;
+    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+    GruTile T;
+    T.m_row = (uint32_t *)smem;
+    T.m_self = (int32_t *)(T.m_row + 64);
+    T.m_t = (float *)(T.m_self + 64);
+    const uint32_t tpad = (p.d_time + 31u) & ~31u;
+    T.s_tw = (float *)(smem + kGruMetaRows);
+    T.s_tb = T.s_tw + tpad;
+    T.hi = (__bf16 *)(smem + p.meta);
+    T.lo = (__bf16 *)(smem + p.off_xl);
+
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+    const uint32_t count = *p.count;
+    const uint64_t j0 = (uint64_t)blockIdx.x * R;
+    if (j0 >= count) return;
+    T.m = (uint32_t)min((uint64_t)R, (uint64_t)count - j0);
+    T.b0 = blockIdx.x * NB;
+    T.stride = 1;
+    if (tid < T.m) {
+        const u32x4 e = p.list[j0 + tid];
+        T.m_row[tid] = e[0];
+        T.m_self[tid] = (int32_t)e[1];
+        T.m_t[tid] = (float)e[3];
+        p.winner[e[1]] = 0ull;
+    }
+    for (uint32_t u = tid; u < tpad; u += kRnnThreads) {
+        T.s_tw[u] = u < p.d_time ? p.tw[u] : 0.0f;
+        T.s_tb[u] = u < p.d_time ? p.tb[u] : 0.0f;
+    }
+    __syncthreads();
+    gru_tile_fill<NB>(p, T);
+    __syncthreads();
+
+    const __bf16 *Xh = T.hi, *Xl = T.lo, *Hh = T.hi + p.kx, *Hl = T.lo + (p.lo_end - p.lo_begin);
+    const uint32_t d = p.d, units = (d + 15u) / 16u, lr = lane & 15u, lk = (lane >> 4) * 8u;
+    for (uint32_t ub = wave; ub < units; ub += kRnnThreads / 64) {
+        const uint32_t j = 16u * ub + lr, jr = j < d ? j : d - 1u;   // rows past d are read, never used
+        // The h values of the blend, loaded before the products so that their
+        // latency overlaps them.
+        float hv[NB][4];
+#pragma unroll
+        for (int rb = 0; rb < NB; rb++)
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                const uint32_t row = 16u * rb + 4u * (lane >> 4) + i;
+                const uint8_t *srow = p.st + (size_t)T.m_self[row < T.m ? row : 0u] * p.srb;
+                hv[rb][i] = p.s_bf16 ? bf16_bits_to_float(((const uint16_t *)srow)[jr]) : ((const float *)srow)[jr];
+            }
+        f32x4 acc[4][NB];   // r, z, input part of n, hidden part of n
+#pragma unroll
+        for (int g = 0; g < 4; g++)
+#pragma unroll
+            for (int rb = 0; rb < NB; rb++) acc[g][rb] = f32x4(0.0f);
+        const u32x4 *wx = p.wpack + (size_t)ub * ((p.kx + p.kd) / 32u) * 192u + lane;
+        gate_seg<NB, false, 2>(acc, Xh, Xl, p.xs, p.ls, p.lo_begin, wx, 0, p.lo_begin, lr, lk);
+        gate_seg<NB, true, 2>(acc, Xh, Xl, p.xs, p.ls, p.lo_begin, wx, p.lo_begin, p.lo_end, lr, lk);
+        gate_seg<NB, false, 2>(acc, Xh, Xl, p.xs, p.ls, p.lo_begin, wx, p.lo_end, p.kx, lr, lk);
+        const u32x4 *wh = wx + (p.kx / 32u) * 192u;
+        if (p.h_lo)
+            gate_seg<NB, true, 3>(acc, Hh, Hl, p.xs, p.ls, 0, wh, 0, p.kd, lr, lk);
+        else
+            gate_seg<NB, false, 3>(acc, Hh, Hl, p.xs, p.ls, 0, wh, 0, p.kd, lr, lk);
+        if (j >= d) continue;
+        const float br = p.b_ih[j] + p.b_hh[j], bz = p.b_ih[d + j] + p.b_hh[d + j];
+        const float bin = p.b_ih[2 * d + j], bhn = p.b_hh[2 * d + j];
+#pragma unroll
+        for (int rb = 0; rb < NB; rb++)
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                const uint32_t row = 16u * rb + 4u * (lane >> 4) + i;
+                if (row >= T.m) continue;
+                const float rg = sigmoid_f32(acc[0][rb][i] + br);
+                const float zg = sigmoid_f32(acc[1][rb][i] + bz);
+                const float ng = tanh_f32(acc[2][rb][i] + bin + rg * (acc[3][rb][i] + bhn));
+                const float out = (1.0f - zg) * ng + zg * hv[rb][i];
+                uint8_t *srow = p.st + (size_t)T.m_self[row] * p.srb;
+                if (p.s_bf16)
+                    ((uint16_t *)srow)[j] = f32_to_bf16_rne(out);
+                else
+                    ((float *)srow)[j] = out;
+            }
+    }
+}
+
 // Weight-stationary form of the GRU pass, for status rows with a 16-byte
 // piece form, kd <= 128, kx + kd <= 32 kWsSteps and a time encoding.  One
 // workgroup per CU with kd / 16 wavefronts: wavefront w holds the weight
@@ -1497,6 +1778,19 @@ uint32_t gru_layout(GruParams &p, uint32_t nb) {
     return p.off_xl + (p.ls ? 16u * nb * p.ls * 2u : 0u);
 }
 
+// Whether rnn_gru_tiles is the faster tiled form for at most `blocks` row
+// blocks of listed rows.  rnn_gru's one form for rows without 16-byte units
+// reads statuses and link rows element by element and spills 140 registers,
+// which costs more than its launches save as soon as a CU has two row blocks
+// (whole update, no node twice: bf16 statuses of 130 beside bf16 link rows of 4,
+// 4000 links 37.9 -> 34.4 us, 20 000 links 142.6 -> 71.8; fp32 statuses of 172
+// beside the same, 20 000 links 184 -> 104, but 200 links 29.2 there and 30.7
+// here), and with up to four unit blocks at any size (bf16 statuses of 33, 600
+// links 19.2 -> 18.3, 20 000 links 59.9 -> 45.5).
+bool tiles_better(const GruParams &p, bool any, uint64_t blocks, uint64_t cus) {
+    return any && (p.d <= 64u || blocks > cus);
+}
+
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // Per-table working memory of the update, grown on demand: the winner
@@ -1699,9 +1993,24 @@ static int rnn_update(nlb_table *h, const int32_t *src, const int32_t *dst, cons
         for (uint32_t st = p.lo_begin / 32; st < p.lo_end / 32; st++) p.ws_lomask |= 1u << st;
     }
     const uint64_t blocks = (pairs + 15) / 16;   // at most (the winners are fewer)
+    // The tiled forms.
+    const int sf = seg_form(p.d, p.srb, status, p.s_bf16);
+    const int ef = p.kx > p.off_e ? seg_form(p.e_dim, p.erb, p.efeat, p.e_bf16) : kSegNone;
+    const bool any = sf == kSegAny || ef == kSegAny;
+    const bool tiles = !ws && tiles_better(p, any, blocks, (uint64_t)cus);
     uint64_t groups = 0;
-    uint32_t nt = p.d <= 64 && blocks > 4u * (uint64_t)cus ? 256 : 512;
-    if (!ws) {
+    uint32_t nt = p.d <= 64 && blocks > 4u * (uint64_t)cus ? 256 : 512, nb = 0;
+    if (tiles) {
+        // Tiles of two row blocks where two workgroups' LDS holds them, of one
+        // when two would give fewer than kGruTargetTiles tiles (counting all 2n
+        // pair rows; the winners are fewer); a tile of one may use a
+        // workgroup's whole LDS.
+        nt = kRnnThreads;
+        nb = pairs >= (uint64_t)kGruTargetTiles * 32u && gru_layout(p, 2) <= kGruLdsMax / 2u ? 2 : 1;
+        lds = gru_layout(p, nb);
+        if (lds > kGruLdsMax) return NLB_EINVAL;   // one 16-row block does not fit the LDS
+        groups = (blocks + nb - 1) / nb;
+    } else if (!ws) {
         // One workgroup of 512 threads per CU; two of 256 for statuses that
         // give eight wavefronts no unit block each, in batches of several tiles
         // per workgroup, where one's row reads then run beside the other's
@@ -1711,7 +2020,7 @@ static int rnn_update(nlb_table *h, const int32_t *src, const int32_t *dst, cons
         // kGruBlocks) and its LDS holds.
         for (;; nt = 512u) {
             groups = nt == 256u ? 2u * (uint64_t)cus : (uint64_t)cus;
-            uint32_t nb = (uint32_t)std::min<uint64_t>(kGruBlocks, (blocks + groups - 1) / groups);
+            nb = (uint32_t)std::min<uint64_t>(kGruBlocks, (blocks + groups - 1) / groups);
             const uint32_t most = nt == 256u ? kGruLdsMax / 2u : kGruLdsMax;
             while (nb && (lds = gru_layout(p, nb)) > most) nb--;
             if (nb) break;
@@ -1789,17 +2098,18 @@ static int rnn_update(nlb_table *h, const int32_t *src, const int32_t *dst, cons
         if (hipLaunchKernel(kern, grid, dim3(128u * kh), args, lds, (hipStream_t)stream) != hipSuccess)
             return NLB_EDEVICE;
     } else {
-        const int sf = seg_form(p.d, p.srb, status, p.s_bf16);
-        const int ef = p.kx > p.off_e ? seg_form(p.e_dim, p.erb, p.efeat, p.e_bf16) : kSegNone;
         const void *kern = nullptr;
-        switch (sf == kSegAny || ef == kSegAny ? -1 : sf * 4 + ef) {
+        switch (tiles ? (int)nb : any ? 0 : 16 + sf * 4 + ef) {
+        case 0: kern = (const void *)rnn_gru<512, kSegAny, kSegNone>; break;
+        case 1: kern = (const void *)rnn_gru_tiles<1>; break;
+        case 2: kern = (const void *)rnn_gru_tiles<2>; break;
 #define NLB_GRU_CASE(SF, EF) \
-        case SF * 4 + EF: kern = nt == 256u ? (const void *)rnn_gru<256, SF, EF> : (const void *)rnn_gru<512, SF, EF>; break;
+        case 16 + SF * 4 + EF: \
+            kern = nt == 256u ? (const void *)rnn_gru<256, SF, EF> : (const void *)rnn_gru<512, SF, EF>; break;
         NLB_GRU_CASE(kSegBf16, kSegNone) NLB_GRU_CASE(kSegBf16, kSegBf16) NLB_GRU_CASE(kSegBf16, kSegF32)
         NLB_GRU_CASE(kSegF32, kSegNone) NLB_GRU_CASE(kSegF32, kSegBf16) NLB_GRU_CASE(kSegF32, kSegF32)
 #undef NLB_GRU_CASE
-        default:
-            kern = nt == 256u ? (const void *)rnn_gru<256, kSegAny, kSegNone> : (const void *)rnn_gru<512, kSegAny, kSegNone>;
+        default: return NLB_EINVAL;
         }
         if (lds > 64u * 1024u &&
             hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kGruLdsMax) != hipSuccess)

@@ -59,6 +59,27 @@ def test_update_tiles_without_time_encoding(case):
     _check_tiles(case)
 
 
+# Rows without a unit form, at more row blocks than CUs: a workgroup per tile of
+# one 16-row block, of two from 32 768 pair rows on; remainders of a tile.
+ANY = [
+    (33, "bf16", 12, 5, "f32", 2053),
+    (33, "bf16", 40, 0, "f32", 16385),
+    (101, "f32", 20, 3, "f32", 2050),
+    (72, "bf16", 33, 4, "bf16", 2049),
+    (128, "f32", 100, 6, "bf16", 16390),
+    (200, "f32", 0, 2, "f32", 2055),        # no time encoding
+    (160, "bf16", 0, 2, "bf16", 16387),
+    (6, "bf16", 0, 0, "f32", 2100),
+    (3, "f32", 5, 12, "bf16", 16400),
+    (1, "bf16", 0, 0, "f32", 1),
+]
+
+
+@pytest.mark.parametrize("case", ANY, ids=_ids)
+def test_update_rows_without_unit_form(case):
+    _check_tiles(case)
+
+
 def _check_tiles(case):
     d, dtype, d_time, e_dim, e_dtype, n = case
     rng = np.random.default_rng(n + d)
