@@ -645,10 +645,10 @@ __device__ __forceinline__ void gru_fill_any(const GruParams &p, const GruTile &
             const uint64_t e = first_eid + (T.m_row[j < T.m ? j : 0u] >> 1);
             if (e < (uint64_t)p.edge_rows) load8(p.efeat + (size_t)e * p.erb, p.e_dim, p.e_bf16, p.e_vec, c, v);
             __bf16 *hi = T.hi + (size_t)j * p.xs + p.off_e + c;
-            if (p.off_e + c < p.lo_end)
-                store_split8(v, hi, T.lo + (size_t)j * p.ls + (p.off_e + c - p.lo_begin));
-            else
+            if (p.e_bf16)
                 store_hi8(v, hi);
+            else
+                store_split8(v, hi, T.lo + (size_t)j * p.ls + (p.off_e + c - p.lo_begin));
         }
     }
 }
@@ -756,12 +756,11 @@ __device__ __forceinline__ void gru_units(const GruParams &p, const GruTile &T, 
     const std::integral_constant<int, 2> x;
     const std::integral_constant<int, 3> h;
     // X's steps 0 .. lb - 1, lb .. le - 1 (those with a lo plane), le .. kxm - 1.
-    // lb is 0 with fp32 statuses, le is kxm with fp32 link rows, and with fp32
-    // statuses and no link rows.  (bf16 statuses without link rows or time
-    // encoding have no lo plane: lb = le = 0.)
+    // lb is 0 with fp32 statuses; le is kxm without bf16 link rows, and where X
+    // has no lo plane (lb = le = kxm).
     if constexpr (SF != kSegF32) segment(no, x, 0u, lb, 0u);
     segment(lo, x, lb, le, 0u);
-    if constexpr (EF == kSegBf16 || (EF == kSegNone && SF != kSegF32)) segment(no, x, le, kxm, 0u);
+    if constexpr (EF == kSegBf16 || SF == kSegAny) segment(no, x, le, kxm, 0u);
     if (SF == kSegF32 || (SF == kSegAny && p.h_lo))
         segment(lo, h, kxm, S, le - lb);
     else
@@ -1060,10 +1059,10 @@ __device__ __forceinline__ void gru_tile_fill(const GruParams &p, const GruTile 
                     store_hi8(v[f], hi);
             } else if (u < ut) {
                 const uint32_t j = nlb_div(u - us, p.ge_m), c = p.off_e + (u - us - j * ge) * 8u;
-                if (p.lo_end == p.kx)
-                    store_split8(v[f], T.hi + (size_t)j * p.xs + c, T.lo + (size_t)j * p.ls + (c - p.lo_begin));
-                else
+                if (p.e_bf16)
                     store_hi8(v[f], T.hi + (size_t)j * p.xs + c);
+                else
+                    store_split8(v[f], T.hi + (size_t)j * p.xs + c, T.lo + (size_t)j * p.ls + (c - p.lo_begin));
             }
         }
     }
@@ -1951,10 +1950,11 @@ static int rnn_update(nlb_table *h, const int32_t *src, const int32_t *dst, cons
     p.kx = p.off_e + pad32(p.e_dim);
     // Columns whose values are not bf16 already: fp32 statuses, the time
     // encoding, fp32 link rows.  They form one range because the time
-    // encoding sits between the other two segments.
+    // encoding sits between the other two segments; without any it is empty
+    // and sits at X's end, so that the columns before it are all of X.
     const bool lo_s = !p.s_bf16, lo_t = p.d_time > 0, lo_e = p.e_dim > 0 && !p.e_bf16;
-    p.lo_begin = lo_s ? 0 : (lo_t ? p.kd : (lo_e ? p.off_e : 0));
-    p.lo_end = lo_e ? p.kx : (lo_t ? p.off_e : (lo_s ? p.kd : 0));
+    p.lo_begin = lo_s ? 0 : (lo_t ? p.kd : (lo_e ? p.off_e : p.kx));
+    p.lo_end = lo_e ? p.kx : (lo_t ? p.off_e : (lo_s ? p.kd : p.kx));
     p.h_lo = lo_s;
     const uint32_t lo_cols = p.lo_end - p.lo_begin + (p.h_lo ? p.kd : 0u);
     p.xs = p.kx + p.kd + 8;
