@@ -203,7 +203,7 @@ __device__ __forceinline__ void stage_rows(const SelectParams &p, const u32x4 *r
     }
 }
 
-constexpr uint64_t kSelectSmall = 256 * 256;   // pair rows up to which select's workgroups have 256 threads
+constexpr uint64_t kSelectSmall = 256 * 256;   // pair rows up to which select's workgroups have 256 threads, twice it: 512
 
 // A workgroup checks T consecutive pair rows, one per thread, collects its
 // winners in LDS (one LDS atomic per wavefront) and appends them to the list
@@ -213,8 +213,9 @@ constexpr uint64_t kSelectSmall = 256 * 256;   // pair rows up to which select's
 // statuses of 128: 55.4 us with 256 threads, 49.1 with 1024).  Smaller ones use
 // 256: the winners' rows are staged by the workgroup that finds them, and 40
 // workgroups of 1024 leave most of the 256 CUs idle (40 000 pair rows, fp32
-// statuses of 100: 66.1 us with 1024 threads, 61.4 with 256; 80 000: 103.7 and
-// 102.8, with bf16 statuses of 128 and popular nodes 37.9 and 38.9).
+// statuses of 100: 66.1 us with 1024 threads, 61.4 with 256); up to twice as many
+// take 512 (80 000, bf16 statuses of 128: 54.9 us with 1024, 53.2 with 512, 54.4
+// with 256).
 template <uint32_t T>
 __global__ __launch_bounds__(T) void rnn_select(SelectParams p) {
     __shared__ u32x4 rows[T];
@@ -1784,10 +1785,35 @@ uint32_t gru_layout(GruParams &p, uint32_t nb) {
 // (whole update, no node twice: bf16 statuses of 130 beside bf16 link rows of 4,
 // 4000 links 37.9 -> 34.4 us, 20 000 links 142.6 -> 71.8; fp32 statuses of 172
 // beside the same, 20 000 links 184 -> 104, but 200 links 29.2 there and 30.7
-// here), and with up to four unit blocks at any size (bf16 statuses of 33, 600
-// links 19.2 -> 18.3, 20 000 links 59.9 -> 45.5).
-bool tiles_better(const GruParams &p, bool any, uint64_t blocks, uint64_t cus) {
-    return any && (p.d <= 64u || blocks > cus);
+// here), and statuses of up to four unit blocks without a unit form at any size
+// (bf16 of 33, 600 links 19.2 -> 18.3, 20 000 links 59.9 -> 45.5).
+//
+// For other rows rnn_gru is ahead while a CU has few row blocks, and later where
+// weights are most of the work; in between its idle wavefronts (eight, or two
+// times eight unit blocks at a time) and its row reads, which little runs
+// beside, cost more than reading the weights once per tile.  The line, from
+// updates of 1000 to 100 000 links without popular nodes, statuses of 40 to 320
+// and link rows of 0 to 186 values (whole update, rnn_gru -> rnn_gru_tiles):
+//   * from 9 row blocks per CU; from 3 where at most five of eight wavefronts
+//     have a unit block (20 000 links: fp32 statuses of 68 57.3 -> 49.7 us, of
+//     100 59.8 -> 55.8, of 192 95.3 -> 93.2, bf16 of 144 79.0 -> 62.2; 14 000
+//     links: bf16 of 144 60.7 -> 54.0, but fp32 of 192 73.6 -> 75.8);
+//   * tiles of two blocks have to fit (fp32 statuses of 192 beside fp32 link rows
+//     of 172, 40 000 links: 204 -> 229), and rows to have piece forms (fp32 of
+//     102: 18 % slower);
+//   * with up to eight unit blocks, at most 12 k-steps or few unit blocks (fp32
+//     statuses of 100 beside bf16 link rows of 186, 100 000 links: 3 % slower);
+//     with up to four, for which rnn_gru has two workgroups of 256 threads, only
+//     bf16 statuses beside wide fp32 link rows (40 beside 172, 40 000 links: 73.3
+//     -> 67.4, but bf16 statuses of 34 without link rows: 4 % slower).
+bool tiles_better(GruParams p, int sf, int ef, uint64_t blocks, uint64_t cus) {
+    if (sf == kSegAny || ef == kSegAny) return blocks > cus || (p.d <= 64u && sf == kSegAny);
+    const uint32_t units = (p.d + 15u) / 16u, steps = (p.kx + p.kd) / 32u;
+    if (p.s_kind < 0 || (p.kx > p.off_e && p.e_kind < 0) || gru_layout(p, 2) > kGruLdsMax / 2u) return false;
+    if (units <= 4u) return p.s_bf16 && ef == kSegF32 && steps > 12u && blocks > 9u * cus;
+    if (units > 14u || (units <= 8u && steps > 12u && (p.s_bf16 || units > 6u))) return false;
+    if (p.s_bf16 && units > 5u && units <= 8u) return false;
+    return blocks > (units <= 5u * ((units + 7u) / 8u) ? 3u : 9u) * cus;
 }
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -1996,10 +2022,9 @@ static int rnn_update(nlb_table *h, const int32_t *src, const int32_t *dst, cons
     // The tiled forms.
     const int sf = seg_form(p.d, p.srb, status, p.s_bf16);
     const int ef = p.kx > p.off_e ? seg_form(p.e_dim, p.erb, p.efeat, p.e_bf16) : kSegNone;
-    const bool any = sf == kSegAny || ef == kSegAny;
-    const bool tiles = !ws && tiles_better(p, any, blocks, (uint64_t)cus);
+    const bool tiles = !ws && tiles_better(p, sf, ef, blocks, (uint64_t)cus);
     uint64_t groups = 0;
-    uint32_t nt = p.d <= 64 && blocks > 4u * (uint64_t)cus ? 256 : 512, nb = 0;
+    uint32_t nt = p.d <= 64 && blocks > 3u * (uint64_t)cus ? 256 : 512, nb = 0;
     if (tiles) {
         // Tiles of two row blocks where two workgroups' LDS holds them, of one
         // when two would give fewer than kGruTargetTiles tiles (counting all 2n
@@ -2014,8 +2039,8 @@ static int rnn_update(nlb_table *h, const int32_t *src, const int32_t *dst, cons
         // One workgroup of 512 threads per CU; two of 256 for statuses that
         // give eight wavefronts no unit block each, in batches of several tiles
         // per workgroup, where one's row reads then run beside the other's
-        // products (20 000 links, bf16 statuses of 34: 64.6 -> 61.3 us; one
-        // tile each, 5000 links, fp32 statuses of 50: 28.1 against 28.7).
+        // products (fp32 statuses of 50 beside fp32 link rows of 172: 8000
+        // links 33.9 -> 30.4 us, but 6000 links 26.8 and 27.5).
         // Tiles of as many row blocks as a workgroup can have (up to
         // kGruBlocks) and its LDS holds.
         for (;; nt = 512u) {
@@ -2072,9 +2097,12 @@ static int rnn_update(nlb_table *h, const int32_t *src, const int32_t *dst, cons
                        a4 ? (p.srb >= 16 ? 16u : 4u) : 2u, 0, 0};
     sp.upr = (p.srb + sp.w - 1) / sp.w;
     sp.upr_m = nlb_div_magic(sp.upr);
-    if (pairs > kSelectSmall)
+    if (pairs > 2u * kSelectSmall)
         hipLaunchKernelGGL(rnn_select<1024>, dim3((unsigned)((pairs + 1023) / 1024)), dim3(1024), 0,
                            (hipStream_t)stream, sp);
+    else if (pairs > kSelectSmall)
+        hipLaunchKernelGGL(rnn_select<512>, dim3((unsigned)((pairs + 511) / 512)), dim3(512), 0, (hipStream_t)stream,
+                           sp);
     else
         hipLaunchKernelGGL(rnn_select<256>, dim3((unsigned)((pairs + 255) / 256)), dim3(256), 0, (hipStream_t)stream,
                            sp);
@@ -2099,7 +2127,7 @@ static int rnn_update(nlb_table *h, const int32_t *src, const int32_t *dst, cons
             return NLB_EDEVICE;
     } else {
         const void *kern = nullptr;
-        switch (tiles ? (int)nb : any ? 0 : 16 + sf * 4 + ef) {
+        switch (tiles ? (int)nb : sf == kSegAny || ef == kSegAny ? 0 : 16 + sf * 4 + ef) {
         case 0: kern = (const void *)rnn_gru<512, kSegAny, kSegNone>; break;
         case 1: kern = (const void *)rnn_gru_tiles<1>; break;
         case 2: kern = (const void *)rnn_gru_tiles<2>; break;

@@ -27,7 +27,8 @@ CASES = [
     (128, "bf16", 100, 0, "f32", 65536, 500),     # merged resolve, few nodes
     (33, "bf16", 12, 6, "bf16", 257, 60),
     (20, "f32", 12, 0, "f32", 32768, 40000),      # 65 536 pair rows: the most for 256-thread select
-    (20, "f32", 12, 0, "f32", 32769, 900),        # one more
+    (20, "f32", 12, 0, "f32", 32769, 900),        # one more: 512 threads
+    (20, "f32", 12, 0, "f32", 65537, 90000),      # 131 074: 1024
 ]
 
 

@@ -80,6 +80,26 @@ def test_update_rows_without_unit_form(case):
     _check_tiles(case)
 
 
+# Batches large enough for a workgroup per tile, rows in piece forms: from 3 row
+# blocks per CU (five, nine and ten unit blocks) and from 9.
+LARGE = [
+    (72, "f32", 33, 10, "bf16", 6150),
+    (68, "bf16", 20, 12, "f32", 6149),
+    (144, "f32", 100, 0, "f32", 6145),
+    (160, "bf16", 100, 24, "bf16", 6146),
+    (100, "f32", 100, 0, "f32", 18433),
+    (172, "f32", 40, 6, "bf16", 18440),
+    (144, "bf16", 0, 0, "f32", 18435),      # no time encoding
+    (144, "bf16", 0, 8, "f32", 16386),
+    (34, "bf16", 100, 172, "f32", 18434),
+]
+
+
+@pytest.mark.parametrize("case", LARGE, ids=_ids)
+def test_update_tiles_of_large_batches(case):
+    _check_tiles(case)
+
+
 def _check_tiles(case):
     d, dtype, d_time, e_dim, e_dtype, n = case
     rng = np.random.default_rng(n + d)
