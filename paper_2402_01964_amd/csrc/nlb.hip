@@ -86,14 +86,13 @@ __device__ __forceinline__ bool link_ok(const InsertParams &p, int32_t u, int32_
 }
 
 // Pass 1.  Each link validates itself and turns into two offer words that
-// go to their slots with a 64-bit atomic maximum.  In all but small batches a
+// go to their slots with a 64-bit atomic maximum.  In large batches a
 // workgroup first merges its links' offers per slot in an LDS hash table (open
 // addressing on the key word's byte offset, 64-bit LDS atomics; merge_max of
 // nlb_internal.h), so a slot that many of its offers hit -- the slots of a
 // popular node -- costs one global atomic per workgroup instead of one per
-// offer; the maximum is associative, so the result is the same.  Small batches
-// skip the merge: they have little same-slot traffic, and the plain atomics
-// finish sooner.
+// offer; the maximum is associative, so the result is the same.  Smaller
+// batches skip the merge (kMergeInsert).
 
 // Validation of link i (ranges; timestamps non-decreasing inside the batch
 // and against the last timestamp of the previous batch) and its two offers.
@@ -145,8 +144,10 @@ __global__ __launch_bounds__(kInsertThreads) void insert_resolve(InsertParams p)
     atomicMax((unsigned long long *)(p.blocks + ov), (unsigned long long)wv);
 }
 
-template <int T>
-__global__ __launch_bounds__(T) void insert_resolve_merged(InsertParams p) {
+constexpr int kInsertMerge = 1024;   // links of a merging workgroup, one per thread
+
+__global__ __launch_bounds__(kInsertMerge) void insert_resolve_merged(InsertParams p) {
+    constexpr int T = kInsertMerge;
     __shared__ unsigned long long merge_off[kMergeEntries<T>];
     __shared__ unsigned long long merge_word[kMergeEntries<T>];
     // The thread's link is loaded (past the batch: the last one again, unused)
@@ -748,10 +749,9 @@ int nlb_insert_batch(nlb_table *h, const int32_t *src, const int32_t *dst, const
     p.key_mode = (uint32_t)h->key_mode;
     p.status = h->status;
     const hipStream_t st = (hipStream_t)stream;
-    if (n >= kMergeLarge)
-        hipLaunchKernelGGL(insert_resolve_merged<1024>, dim3((n + 1023) / 1024), dim3(1024), 0, st, p);
-    else if (n >= kMergeInsert)
-        hipLaunchKernelGGL(insert_resolve_merged<512>, dim3((n + 511) / 512), dim3(512), 0, st, p);
+    if (n >= kMergeInsert)
+        hipLaunchKernelGGL(insert_resolve_merged, dim3((n + kInsertMerge - 1) / kInsertMerge), dim3(kInsertMerge), 0,
+                           st, p);
     else
         hipLaunchKernelGGL(insert_resolve, dim3((n + kInsertThreads - 1) / kInsertThreads),
                            dim3(kInsertThreads), 0, st, p);

@@ -161,16 +161,21 @@ __device__ __forceinline__ SlotLds read_slot(const uint8_t *blocks, uint32_t blo
 // popular node's slot or word takes one per link that has it (50 000 links with
 // power-law endpoints: the hottest node kept the launch waiting for 100 us).
 // What it costs: the table's clearing and probing, about 2 us.
-// Updates of the statuses merge from 1024 links (1 000 000 nodes, popularity
-// exponent 1.05: 10 000 links 49.4 us plain, 31.6 merged, 50 000 links 142.6 and
-// 43.6; exponent 0.5, 10 000 links: 29.3 and 31.1), insertions, whose offers
-// spread over a node's slots, from 32768 (exponent 1.05: 10 000 links 11.3 us
-// plain, 10.2 merged, 30 000 links 23.6 and 13.2; exponent 0.5, 10 000 links 7.4
-// and 9.3, 30 000 links 9.1 and 11.7).  Larger batches take larger workgroups,
-// which send a popular address's maximum fewer times (insertion of 60 000 links,
-// exponent 1.05: 28.9 us with 256 threads, 19.4 with 512, 15.4 with 1024).
-constexpr uint32_t kMergeUpdate = 1024, kMergeInsert = 32768;   // links from which batches merge
-constexpr uint32_t kMergeMid = 16384, kMergeLarge = 65536;      // links from which workgroups have 512, 1024 threads
+// Updates of the statuses, where a link's word is its node's, merge from 1024
+// links (1 000 000 nodes, popularity exponent 1.05: 10 000 links 49.4 us plain,
+// 31.6 merged, 50 000 links 142.6 and 43.6; exponent 0.5, 10 000 links: 29.3 and
+// 31.1).  Insertions, whose offers spread over a node's slots, merge from 65536
+// (100 000 nodes, exponent 1.05: 65 000 links 50.2 us plain, 65 536 merged 15.3;
+// exponent 0.5: 13.7 and 17.3).  Below that they stay plain: smaller batches
+// would gain as much with popular nodes (50 000 links, exponent 1.05: 39.9 us
+// plain, 17.3 merged by workgroups of 512), but lose 10 to 37 percent without
+// (11.6 and 13.4 us; 32 768 links 9.3 and 12.5).  Larger batches take larger
+// workgroups, which send a popular address's maximum fewer times (update of
+// 65 000 links, exponent 1.05: 50.6 us with 256 threads, 44.4 with 512, 42.1 with
+// 1024; 10 000 links, exponent 0.5: 30.2, 32.3, 33.9).
+constexpr uint32_t kMergeUpdate = 1024;                      // links from which updates merge
+constexpr uint32_t kMergeMid = 16384, kMergeLarge = 65536;   // links from which workgroups have 512, 1024 threads
+constexpr uint32_t kMergeInsert = kMergeLarge;               // links from which insertions merge
 // Table entries, for up to two addresses per link: load <= 1/2.
 template <int T> constexpr int kMergeBits = 1 + kMergeBits<T / 2>;
 template <> constexpr int kMergeBits<1> = 2;

@@ -1,6 +1,7 @@
-"""Insertion at the batch sizes where its resolve launch changes: plain
-atomics, offers merged by workgroups of 512 links, of 1024.  Graphs with a hub
-(most offers on a few slots) and without; two batches, the table against the oracle's after each."""
+"""Insertion around the batch size where its resolve launch changes (65 536
+links: plain atomics, then offers merged by workgroups of 1024 links) and at
+half of it.  Graphs with a hub (most offers on a few slots) and without; two
+batches, the table against the oracle's after each."""
 import numpy as np
 import pytest
 
