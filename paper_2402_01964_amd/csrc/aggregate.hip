@@ -1684,8 +1684,9 @@ __global__ __launch_bounds__(kRowThreads) __attribute__((amdgpu_waves_per_eu(2, 
 // node rows of 100 and link rows of 172 values: 734 us in the tiled kernel,
 // 62 us here (83 with the masks on every step and the registers spilling: a
 // reload in the block loop also waits for the row requests before it).  The
-// smallest launches gain as well (414 queries of 10 slots, bf16 rows of 128:
-// 14.0 -> 11.7 us), so no size is left to the tiled kernel.
+// smallest launches of wide rows gain as well (414 queries of 10 slots, bf16 rows
+// of 128: 14.0 -> 11.7 us); narrow ones stay with the tiled kernel
+// (tiled_better).
 constexpr int kRowNone = 0, kRowBf16 = 1, kRowF32 = 2;
 constexpr int kGroupNodeSteps = 4, kGroupEdgeSteps = 6, kGroupTimeSteps = 4;   // k-steps of an instance at most
 constexpr uint32_t kGroupMaxS = 64;
@@ -2224,6 +2225,29 @@ __global__ __launch_bounds__(kRowThreads) __attribute__((amdgpu_waves_per_eu(2, 
     }
 }
 
+// Whether the tiled kernel is faster than aggregate_groups for a launch.  Up to
+// about half a query per wavefront a launch takes as long as its first group,
+// and aggregate_groups runs through all k-steps of its instance (fp32 rows three
+// times as many instructions as bf16 ones) and through blocks of 16 slots, where
+// a tile of one query has the k-steps that the widths need: its time grows with
+// them, with the slots and with widths that cut its pieces of 8 values.
+// 20 slots, fp32 node rows of 4 and link rows of 4 values, 600 queries: 17.0 us
+// tiled, 19.3 in groups; 5 slots, rows of 20 and 30, 100 time columns, two heads,
+// 300 queries: 13.7 and 17.1; but rows of 100 and 172, 10 slots: 21.0 and 16.1.
+// The limits, by kinds of rows and by heads, are fitted to 2900 launches of 8 to
+// 1100 queries, 1 to 48 slots and 42 shapes: the choice costs 1.2 % in the root
+// mean square, and 10 % where a launch of the most slots lies at the line.
+bool tiled_better(const AggParams &p, uint64_t cus) {
+    if (p.nq > cus * 9u / 2u) return false;
+    static const uint32_t limit[2][3][2] = {{{12, 12}, {32, 48}, {0, 0}},           // node or link rows
+                                            {{36, 36}, {64, 96}, {124, 172}}};     // both
+    const uint32_t rows = (p.n_dim ? 1u : 0u) + (p.e_dim ? 1u : 0u);
+    const uint32_t f32 = (p.n_dim && !p.n_bf16 ? 1u : 0u) + (p.e_dim && !p.e_bf16 ? 1u : 0u);
+    const uint32_t cut = (p.n_dim % 8u ? 1u : 0u) + (p.e_dim % 8u ? 1u : 0u) + (p.d_time % 8u ? 1u : 0u);
+    const uint32_t slots = p.s - 4u * ((p.s + 15u) / 16u - 1u);
+    return rows && (slots + 6u) * (p.k1 / 32u) + 6u * cut + p.nq / 25u <= limit[rows - 1u][f32][p.heads == 2u ? 1 : 0];
+}
+
 // LDS layout of a tile with `rows` slot rows and `qrows` query rows.
 uint32_t agg_layout(AggParams &p, uint32_t rows, uint32_t qrows) {
     p.rows = rows;
@@ -2307,9 +2331,9 @@ extern "C" int nlb_aggregate(nlb_table *h, const int32_t *node, const uint32_t *
     p.status = h->status;
     p.heads = heads;
 
-    // The wavefront-per-query kernel, for the input shapes it is instantiated
-    // for (those of the synthetic workloads) when its weights fit one
-    // workgroup's LDS; other shapes take the tiled kernel.
+    // The wavefront-per-query kernels, for the input shapes they are
+    // instantiated for (those of the synthetic workloads) when their weights fit
+    // one workgroup's LDS; other shapes take aggregate_groups or the tiled kernel.
     const uint32_t nks = p.off_e / 32, eks = (p.off_t - p.off_e) / 32, tks = (p.k1 - p.off_t) / 32;
     const int nkind = nks ? piece_kind(p.nrb, p.nfeat, p.n_bf16) : 0;
     const int ekind = eks ? piece_kind(p.erb, p.efeat, p.e_bf16) : 0;
@@ -2365,9 +2389,9 @@ extern "C" int nlb_aggregate(nlb_table *h, const int32_t *node, const uint32_t *
         // more heads take the tiled kernel.  Wide link rows without node rows
         // (161 to 192 values) leave most of a per-query block's time to its
         // empty rows: aggregate_groups is faster as soon as a wavefront has two
-        // queries (20 slots, fp32 rows of 172 values: 4500 queries 32.9 us per
-        // query, 27.4 grouped, 12 000 queries 57.6 and 45.3, 1800 queries 18.4
-        // and 18.8; 10 slots, 12 000 queries 38.1 and 29.7), and at any size for
+        // queries (20 slots, fp32 rows of 172 values: 4500 queries 32.9 us in the
+        // per-query kernel, 27.4 grouped, 12 000 queries 57.6 and 45.3, 1800 queries
+        // 18.4 and 18.8; 10 slots, 12 000 queries 38.1 and 29.7), and at any size for
         // rows at 4-byte alignment, which it reads in 16-byte units (bf16 rows of
         // 186 values: 1800 queries 19.4 and 16.3, 12 000 queries 62.8 and 38.2).
         // Narrower link rows, or node rows beside them, stay with the per-query
@@ -2376,8 +2400,8 @@ extern "C" int nlb_aggregate(nlb_table *h, const int32_t *node, const uint32_t *
                              (ekind == kBf16Word || r.gq >= 2);
         const bool rows_ok = heads <= 2 && !grouped;
 #define NLB_ROWS_SHAPE(A, B, C, NK, EK)                                                              \
-    if (!kern && rows_ok && nkind >= 0 && ekind >= 0 && nks == A && eks == B && tks == C && (A == 0 || nkind == NK) &&            \
-        (B == 0 || ekind == EK)) {                                                                    \
+    if (!kern && rows_ok && nkind >= 0 && ekind >= 0 && nks == A && eks == B && tks == C &&           \
+        (A == 0 || nkind == NK) && (B == 0 || ekind == EK)) {                                         \
         if (packed && heads == 1) {                                                                   \
             kern = (const void *)aggregate_packed<A, B, C, NK, EK, 1>;                                \
             bytes = PackedLayout<A + B + C, A + 2, C, 1>::bytes;                                      \
@@ -2426,13 +2450,14 @@ extern "C" int nlb_aggregate(nlb_table *h, const int32_t *node, const uint32_t *
     }
 
     // Other shapes inside aggregate_groups' k-steps, with rows of at least one
-    // 16-byte load: 1.1 to 12 times as fast there as in the tiled kernel, for
-    // 300 to 25 000 queries of 8 to 20 slots.  (What is left for the tiled
-    // kernel: more than two heads, wider rows, rows of less than 16 bytes.)
+    // 16-byte load: 1.2 to 12 times as fast there as in the tiled kernel from
+    // 1500 queries on.  (What is left for the tiled kernel: small launches of
+    // narrow rows, more than two heads, wider rows, rows of less than 16 bytes.)
     const int nk = p.n_dim ? (p.n_bf16 ? kRowBf16 : kRowF32) : kRowNone;
     const int ek = p.e_dim ? (p.e_bf16 ? kRowBf16 : kRowF32) : kRowNone;
     if (heads <= 2 && h->s <= kGroupMaxS && nks <= (uint32_t)kGroupNodeSteps && eks <= (uint32_t)kGroupEdgeSteps &&
-        tks <= (uint32_t)kGroupTimeSteps && (!nk || p.n_dim >= row_unit(nk)) && (!ek || p.e_dim >= row_unit(ek))) {
+        tks <= (uint32_t)kGroupTimeSteps && (!nk || p.n_dim >= row_unit(nk)) && (!ek || p.e_dim >= row_unit(ek)) &&
+        !tiled_better(p, (uint64_t)cus)) {
         r.k1 = p.k1;
         r.off_e = p.off_e;
         r.off_t = p.off_t;

@@ -69,7 +69,20 @@ def test_wide_link_rows_match_oracle(case):
     _check_against_oracle(case, lambda t: t)
 
 
-def _check_against_oracle(case, place):
+# Around the number of queries up to which narrow rows stay with the tiled
+# kernel (1152 on 256 CUs, fewer for wider rows or more slots).
+SMALL = [((16, "f32", 16, "f32", 16, 10, 2), (1152, 1153)), ((64, "f32", 30, "f32", 100, 3, 1), (1152, 1153)),
+         ((8, "bf16", 9, "f32", 8, 12, 1), (124, 125)), ((0, "f32", 8, "bf16", 0, 3, 1), (99, 100)),
+         ((0, "f32", 20, "f32", 20, 4, 2), (424, 425)), ((16, "f32", 0, "f32", 8, 7, 1), (174, 175)),
+         ((5, "f32", 6, "f32", 7, 33, 1), (24, 1152))]
+
+
+@pytest.mark.parametrize("case,nqs", SMALL, ids=[_ids(c) for c, _ in SMALL])
+def test_small_launches_match_oracle(case, nqs):
+    _check_against_oracle(case, lambda t: t, nqs)
+
+
+def _check_against_oracle(case, place, nqs=(1, 37, 5003, 40001)):
     import paper_2402_01964_amd as nlb
     dn, nt, de, et, d_time, s, heads = case
     base = synth.workload(1)
@@ -92,7 +105,7 @@ def _check_against_oracle(case, place):
     rng = np.random.default_rng(11 * dn + de)
     ends = np.concatenate([src, dst, neg])
     worst = 0.0
-    for nq in (1, 37, 5003, 40001):
+    for nq in nqs:
         q = ends[rng.integers(0, len(ends), nq)].astype(np.int32)
         tq = rng.integers(0, int(t[-1]) + 2, nq).astype(np.uint32)
         tq[-1] = int(t[-1]) + 1
