@@ -1682,22 +1682,15 @@ __global__ __launch_bounds__(kRowThreads) __attribute__((amdgpu_waves_per_eu(2, 
 // Bound by vector-ALU issue, as aggregate_packed, and three instructions per
 // value for the split of fp32 rows.  12 000 queries, 20 slots, fp32
 // node rows of 100 and link rows of 172 values: 734 us in the tiled kernel,
-// 62 us here (83 with the masks on every step and the registers spilling: a
-// reload in the block loop also waits for the row requests before it).  The
-// smallest launches of wide rows gain as well (414 queries of 10 slots, bf16 rows
+// 62 us here (83 with the masks on every step and more registers spilling: a
+// reload in the block loop also waits for the row requests before it; that
+// instance still spills 20, with two heads 32, and those of bf16 beside fp32
+// rows with two heads 15 to 19).  The smallest launches of wide rows gain as well (414 queries of 10 slots, bf16 rows
 // of 128: 14.0 -> 11.7 us); narrow ones stay with the tiled kernel
 // (tiled_better).
 constexpr int kRowNone = 0, kRowBf16 = 1, kRowF32 = 2;
 constexpr int kGroupNodeSteps = 4, kGroupEdgeSteps = 6, kGroupTimeSteps = 4;   // k-steps of an instance at most
 constexpr uint32_t kGroupMaxS = 64;
-
-// A uniform value that the compiler re-reads where it is used (keeps what
-// follows from it out of long-lived registers).
-__device__ __forceinline__ uint32_t opaque_u32(uint32_t x) {
-    x = __builtin_amdgcn_readfirstlane(x);
-    asm volatile("" : "+s"(x));
-    return x;
-}
 
 struct GroupParams : RowParams {
     uint32_t k1, off_e, off_t, k3;   // row widths of w1 / w3, first columns of the link rows and of the encoding in w1

@@ -151,6 +151,14 @@ __device__ __forceinline__ SlotLds read_slot(const uint8_t *blocks, uint32_t blo
     return decode_slot(((const uint64_t *)blk)[a], ((const int32_t *)(blk + 8u * s))[a], tq);
 }
 
+// A uniform value that the compiler re-reads where it is used (keeps what
+// follows from it, or a loop invariant flag, out of long-lived registers).
+__device__ __forceinline__ uint32_t opaque_u32(uint32_t x) {
+    x = __builtin_amdgcn_readfirstlane(x);
+    asm volatile("" : "+s"(x));
+    return x;
+}
+
 // ---------------------------------------------------------------- LDS max-merge
 // Open-addressing LDS table that merges 64-bit maxima per global address
 // (byte offset `off`): merge_max records max(word) for off, so one global

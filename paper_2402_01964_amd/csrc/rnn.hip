@@ -28,8 +28,9 @@
 //   gru      where its registers suffice, the weight-stationary form
 //            (rnn_gru_ws: one workgroup per CU keeps the weights in
 //            registers and loops over 32-row tiles of listed rows);
-//            otherwise a workgroup takes tiles of up to three 16-row blocks
-//            and reads the weights from L2 (rnn_gru).  Both build the inputs
+//            otherwise workgroups take tiles of up to three 16-row blocks and
+//            read the weights from L2: one or two persistent workgroups per CU
+//            (rnn_gru), or one per tile (rnn_gru_tiles).  All build the inputs
 //            in LDS and run both GRU products on bf16 matrix cores; the
 //            gates, the blend with h and the rounding to the status type
 //            happen in registers, and the new status goes over the old one.
@@ -223,51 +224,25 @@ __global__ __launch_bounds__(T) void rnn_select(SelectParams p) {
     const uint32_t lane = threadIdx.x & 63;
     if (threadIdx.x == 0) n_local = 0;
     __syncthreads();
-    // A thread's pair rows: their links' endpoints, then the winner words
-    // of their nodes, are read in two rounds of unconditional loads (rows
-    // past the batch re-read the last link; invalid endpoints read
-    // winner[0]) before any is used.
-    constexpr int RS = T / T;
-    const uint64_t r0 = (uint64_t)blockIdx.x * T;
-    int32_t su[RS], sv[RS];
-    uint32_t st[RS];
-#pragma unroll
-    for (int q = 0; q < RS; q++) {
-        const uint64_t r = min(r0 + q * T + threadIdx.x, 2ull * p.n - 1ull);
-        su[q] = p.src[(uint32_t)(r >> 1)];
-        sv[q] = p.dst[(uint32_t)(r >> 1)];
-        st[q] = p.t[(uint32_t)(r >> 1)];
-    }
-    unsigned long long wv[RS];
-#pragma unroll
-    for (int q = 0; q < RS; q++) {
-        const uint64_t r = min(r0 + q * T + threadIdx.x, 2ull * p.n - 1ull);
-        const int32_t self = (r & 1) ? sv[q] : su[q];
-        wv[q] = p.winner[endpoints_ok(su[q], sv[q], p.num_nodes) ? self : 0];
-    }
-#pragma unroll
-    for (int q = 0; q < RS; q++) {
-        const uint32_t k = q * T + threadIdx.x;
-        const uint64_t r = r0 + k;
-        bool win = false;
-        int32_t self = -1, other = -1;
-        if (r < 2ull * p.n) {
-            const int32_t u = su[q], v = sv[q];
-            if (endpoints_ok(u, v, p.num_nodes)) {
-                self = (r & 1) ? v : u;
-                other = (r & 1) ? u : v;
-                win = wv[q] == r + 1;
-            }
-        }
-        const uint64_t mask = __ballot(win);
-        if (mask == 0) continue;
+    // The thread's pair row: its link's endpoints, then the winner word of its
+    // node, read unconditionally (rows past the batch re-read the last link;
+    // invalid endpoints read winner[0]).
+    const uint64_t row = (uint64_t)blockIdx.x * T + threadIdx.x, r = min(row, 2ull * p.n - 1ull);
+    const int32_t u = p.src[(uint32_t)(r >> 1)], v = p.dst[(uint32_t)(r >> 1)];
+    const uint32_t t = p.t[(uint32_t)(r >> 1)];
+    const bool ok = endpoints_ok(u, v, p.num_nodes);
+    const int32_t self = (r & 1) ? v : u, other = (r & 1) ? u : v;
+    const unsigned long long won = p.winner[ok ? self : 0];
+    const bool win = row == r && ok && won == r + 1;
+    const uint64_t mask = __ballot(win);
+    if (mask != 0) {
         const uint32_t leader = (uint32_t)__ffsll((long long)mask) - 1u;
         uint32_t off = 0;
         if (lane == leader) off = atomicAdd(&n_local, (uint32_t)__popcll(mask));
         off = __shfl(off, (int)leader);
         if (win)
             rows[off + (uint32_t)__popcll(mask & ((1ull << lane) - 1ull))] =
-                u32x4{(uint32_t)r, (uint32_t)self, (uint32_t)other, st[q]};
+                u32x4{(uint32_t)r, (uint32_t)self, (uint32_t)other, t};
     }
     __syncthreads();
     // The workgroup's place in the list and the list entries, while the first
@@ -288,18 +263,14 @@ __global__ __launch_bounds__(T) void rnn_select(SelectParams p) {
 }
 
 struct GruParams {
-    const int32_t *src;
-    const int32_t *dst;
     const uint32_t *t;
     uint32_t n;
-    int64_t num_nodes;
     const u32x4 *list;                  // winners {pair row, self, other, link time} (select)
     const uint32_t *count;
     uint64_t first_eid;                 // arrival index (link-row index) of link 0, or NLB_EID_LAST_BATCH
     const uint32_t *table_status;       // the table's device status words (its link count)
     uint32_t d, d_time;
     const float *tw, *tb;               // time encoding
-    uint32_t t_vec;                     // tw, tb 16-byte aligned
     const uint8_t *efeat;
     int64_t edge_rows;
     uint32_t e_dim, e_bf16, erb, e_vec;
@@ -318,9 +289,8 @@ struct GruParams {
     int32_t s_kind, e_kind;             // piece forms of status / link rows (-1: none applies)
     uint32_t meta;                      // LDS bytes before X: row list, then T-enc w | b (pad32(d_time) each)
     uint32_t ws_lomask;                 // weight-stationary form: bit s set if X k-step s has a lo plane
-    const __bf16 *w_ih, *w_hh;
     const float *b_ih, *b_hh;
-    const u32x4 *wpack;                 // the weights in operand-fragment order (rnn_select)
+    const u32x4 *wpack;                 // the weights in operand-fragment order (pack_weights)
 };
 
 // Arrival index of link 0 of the batch: given, or (NLB_EID_LAST_BATCH) the
@@ -417,9 +387,11 @@ __device__ __forceinline__ void fill_seg(uint32_t units, uint32_t g, uint64_t g_
 // wavefronts as well.  At larger ones the weights' way from L2 (a CU's 64
 // bytes a clock) and the matrix instructions bound it.
 //
-// Measured: 600 links, fp32 statuses of 100, fp32 link rows of 172:
-// 15.0 -> 11.6 us; 10 000 links, bf16 link rows of 186: 25.6 -> 20.6 us (the
-// form of 256-thread workgroups, a tile each, that this one took the place of).
+// Measured, against a workgroup per tile: 600 links, fp32 statuses of 100, fp32
+// link rows of 172: 15.0 -> 11.6 us; 10 000 links, bf16 link rows of 186: 25.6 ->
+// 20.6 us.  Larger batches, where little runs beside the one or two workgroups
+// of a CU, go to rnn_gru_tiles (tiles_better).  The instances for rows in units
+// use all 256 registers and spill 11 to 14, the one for other rows 140.
 constexpr int kGruRing = 4;
 constexpr int kGruBlocks = 3;      // row blocks of a tile at most
 
@@ -890,7 +862,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
 // `as`; the lo plane starts at column lo_b with its own stride `ls`)
 //              * W_g^T for the three gates, over the k-steps kb, kb + 32, ..
 // < ke; g' = g for the r and z gates and g' = NIDX for the n gate.  LO adds
-// the lo-plane products.  The weights come packed (rnn_resolve): wp points at
+// the lo-plane products.  The weights come packed (pack_weights): wp points at
 // this lane's word of the fragment (k-step 0, gate 0) of the matrix and unit
 // block; fragment (k-step s, gate g) is 192 s + 64 g words on.
 template <int NB, bool LO, int NIDX>
@@ -1221,14 +1193,6 @@ __device__ __forceinline__ uint32_t frag_off(uint32_t j, uint32_t c) {
     return (((c >> 5) * (kWsRows / 16) + (j >> 4)) * 64u + (j & 15u) + 16u * ((c >> 3) & 3u)) * 16u;
 }
 
-// A uniform value that the compiler re-reads where it is used (keeps loop
-// invariant flags out of long-lived registers).
-__device__ __forceinline__ uint32_t opaque_u32(uint32_t x) {
-    x = __builtin_amdgcn_readfirstlane(x);
-    asm volatile("" : "+s"(x));
-    return x;
-}
-
 typedef __attribute__((address_space(3))) void *lds_ptr;
 
 // One direct global-to-LDS load of 16 bytes per lane: lane l's bytes from g
@@ -1290,7 +1254,7 @@ __global__ __launch_bounds__(128 * KH) void rnn_gru_ws(GruParams p) {
     __shared__ __attribute__((aligned(16))) uint8_t bs1[L::s_bytes];
     __shared__ __attribute__((aligned(16))) uint8_t bt0[L::t_bytes];
     __shared__ __attribute__((aligned(16))) uint8_t bt1[L::t_bytes];
-    // Row lists {pair row, self, other, 0} of 1 KB slots (R entries and room
+    // Row lists {pair row, self, other, link time} of 1 KB slots (R entries and room
     // for the duplicates a direct load of R entries writes); tile i in slot
     // i % 8.  Link times of the rows of tile i in row i % 4 of tt (words
     // R .. 63 of a row: room for the duplicates a direct load writes).
@@ -1519,7 +1483,7 @@ __global__ __launch_bounds__(128 * KH) void rnn_gru_ws(GruParams p) {
         lds_load4(p.t + (meta[MS + (lane & (R - 1))][0] >> 1), lds_addr(tt[1]));
     }
     __builtin_amdgcn_sched_barrier(0);
-    {   // this wavefront's fragments, 1 KB each, contiguous (packed by rnn_select;
+    {   // this wavefront's fragments, 1 KB each, contiguous (packed by rnn_resolve;
         // X steps past kx_steps re-read the last one, unused)
         const u32x4 *wf = p.wpack + (size_t)wave * (kx_steps + KH) * 192u + lane;
 #pragma unroll
@@ -1949,18 +1913,14 @@ static int rnn_update(nlb_table *h, const int32_t *src, const int32_t *dst, cons
 
     GruParams p;
     std::memset(&p, 0, sizeof(p));
-    p.src = src;
-    p.dst = dst;
     p.t = t;
     p.n = n;
-    p.num_nodes = h->num_nodes;
     p.first_eid = first_eid;
     p.table_status = h->status;
     p.d = (uint32_t)wts->status_dim;
     p.d_time = h->d_time;
     p.tw = h->w;
     p.tb = h->b;
-    p.t_vec = ((uintptr_t)h->w | (uintptr_t)h->b) % 16 == 0;
     p.efeat = h->efeat;
     p.edge_rows = h->edge_rows;
     p.e_dim = h->erb / e_es;
@@ -1991,8 +1951,6 @@ static int rnn_update(nlb_table *h, const int32_t *src, const int32_t *dst, cons
     p.s_kind = piece_kind(p.srb, status, p.s_bf16);
     p.e_kind = h->efeat ? piece_kind(h->erb, h->efeat, p.e_bf16) : -1;
     p.meta = align16(kGruMetaRows + 8u * pad32(p.d_time));
-    p.w_ih = (const __bf16 *)wts->w_ih;
-    p.w_hh = (const __bf16 *)wts->w_hh;
     p.b_ih = wts->b_ih;
     p.b_hh = wts->b_hh;
 
@@ -2074,7 +2032,7 @@ static int rnn_update(nlb_table *h, const int32_t *src, const int32_t *dst, cons
     p.o_vec = p.srb % 16 == 0;
 
     ResolveParams rp = {src, dst, n, h->num_nodes, wk.winner, h->status, count, 0,
-                        p.w_ih, p.w_hh, (u32x4 *)wk.wpack, p.d, p.kx, p.kd, p.kx / 32, (p.kx + p.kd) / 32,
+                        (const __bf16 *)wts->w_ih, (const __bf16 *)wts->w_hh, (u32x4 *)wk.wpack, p.d, p.kx, p.kd, p.kx / 32, (p.kx + p.kd) / 32,
                         (uint32_t)(wpack_bytes / 16)};
     // (the weight pack by workgroups of its own: one piece per thread)
     const uint32_t rt = n >= kMergeLarge ? 1024u : n >= kMergeMid ? 512u : 256u;
