@@ -108,7 +108,7 @@ def sample_bytes(w, valid_slots, queries):
 COUNTER_SOURCES = {
     "nlb_sample": ("sample_gather_{}.md", ("nlb.hip", "nlb_internal.h", "nlb_divide.h")),
     "nlb_aggregate": ("aggregate_packed_{}.md",
-                      ("aggregate.hip", "nlb_internal.h", "nlb_pieces.h", "nlb_divide.h")),
+                      ("aggregate.hip", "nlb_internal.h", "nlb_pieces.h", "nlb_divide.h", "nlb_units.h")),
 }
 
 
@@ -953,7 +953,7 @@ def main():
         fl = rnn_flops(w, d_r, winners)
         rb = rnn_bytes(w, d_r, status.element_size(), links, winners)
         t_s = rnn_ms.sum() * 1e-3
-        res["rnn"] = {"kernels": "rnn_resolve(_merged) + rnn_select + rnn_gru_ws (or rnn_gru) + rnn_scatter",
+        res["rnn"] = {"kernels": "rnn_resolve(_merged) + rnn_select + rnn_gru_ws (or rnn_gru, rnn_gru_tiles)",
                       "status": f"{d_r} x {str(status.dtype).replace('torch.', '')}",
                       "links_per_s": links / t_s, "node_updates_per_s": winners / t_s,
                       "ms_avg": float(rnn_ms.mean()), "updates_per_batch": winners / K,
