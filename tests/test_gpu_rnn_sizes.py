@@ -1,9 +1,10 @@
 """The status update at the sizes where its launches change.
 
-Batches around the sizes at which select takes larger workgroups and resolve
-merges in LDS, with statuses copied in every unit (16, 8, 4 and 2 bytes), on
-graphs so small that most rows are read as another node's r_other while their
-own status is rewritten.  Two batches in a row: the winner words have to be
+Batches on both sides of the sizes at which resolve merges in LDS (1024 links)
+and both launches take larger workgroups (resolve at 16384 and 65536 links,
+select past 65536 and 131072 pair rows), with statuses copied in every unit (16,
+4 and 2 bytes), some on graphs so small that most rows are read as another
+node's r_other while their own status is rewritten.  Two batches in a row: the winner words have to be
 zero again after the first.
 """
 import numpy as np
@@ -20,15 +21,19 @@ pytestmark = pytest.mark.gpu
 CASES = [
     (100, "f32", 100, 0, "f32", 16384, 9000),     # merged by workgroups of 512 links from here on
     (100, "f32", 12, 0, "f32", 16385, 30000),
-    (50, "f32", 20, 6, "f32", 16385, 700),        # 8-byte units
-    (33, "f32", 12, 5, "f32", 17001, 30000),      # 4-byte units
+    (50, "f32", 20, 6, "f32", 16385, 700),        # rows of 200 bytes
+    (33, "f32", 12, 5, "f32", 17001, 30000),      # rows that 16-byte units overlap in (132 bytes)
     (33, "bf16", 12, 6, "bf16", 17001, 30000),    # 2-byte units
-    (128, "bf16", 100, 0, "f32", 65535, 40000),   # unmerged resolve, weight-stationary pass
-    (128, "bf16", 100, 0, "f32", 65536, 500),     # merged resolve, few nodes
+    (128, "bf16", 100, 0, "f32", 65535, 40000),   # the most merged 512 links at a time, weight-stationary pass
+    (128, "bf16", 100, 0, "f32", 65536, 500),     # merged 1024 at a time, few nodes
     (33, "bf16", 12, 6, "bf16", 257, 60),
     (20, "f32", 12, 0, "f32", 32768, 40000),      # 65 536 pair rows: the most for 256-thread select
     (20, "f32", 12, 0, "f32", 32769, 900),        # one more: 512 threads
     (20, "f32", 12, 0, "f32", 65537, 90000),      # 131 074: 1024
+    (20, "f32", 12, 0, "f32", 1023, 30),          # the most that resolve without a merge
+    (20, "f32", 12, 0, "f32", 1024, 30),          # merged 256 links at a time
+    (20, "f32", 12, 0, "f32", 16383, 400),        # the most of these
+    (3, "f32", 12, 4, "f32", 3001, 500),          # 4-byte units (rows of 12 bytes)
 ]
 
 

@@ -12,7 +12,7 @@ import pytest
 
 import paper_2402_01964_amd as nlb
 import synth
-from tests.gpu_helpers import feat_to_dev
+from tests.gpu_helpers import feat_to_dev, to_dev
 from tests.test_gpu_rnn import _check_batch, _log, _small_table, _weights_dev
 
 pytestmark = pytest.mark.gpu
@@ -98,6 +98,41 @@ LARGE = [
 @pytest.mark.parametrize("case", LARGE, ids=_ids)
 def test_update_tiles_of_large_batches(case):
     _check_tiles(case)
+
+
+@pytest.mark.parametrize("case", [(144, "f32", 100, 0, "f32", 6145), (33, "bf16", 12, 5, "f32", 2053)], ids=_ids)
+def test_update_tiles_captured_and_without_allocation(case):
+    """Three updates in a row: eager, from the static array, and as replays of
+    one HIP graph with other work of the program between them -- bit for bit
+    the same statuses."""
+    import torch
+    d, dtype, d_time, e_dim, e_dtype, n = case
+    rng = np.random.default_rng(n)
+    N = 2 * n + 5
+    ef = rng.standard_normal((n, e_dim)).astype(np.float32) if e_dim else None
+    g, _, _ = _small_table(N, d_time, feat_to_dev(ef, e_dtype) if e_dim else None)
+    st = rng.standard_normal((N, d)).astype(np.float32)
+    st = feat_to_dev(synth._to_bf16_bits(st) if dtype == "bf16" else st, dtype)
+    W = _weights_dev(synth.gru_weights_for(d, d_time, e_dim, 5))
+    ends = rng.permutation(N)[:2 * n].astype(np.int32)
+    args = [to_dev(np.ascontiguousarray(x)) for x in (ends[:n], ends[n:], np.sort(rng.integers(0, 10**6, n)).astype(np.uint32))]
+    eager, fixed, graph = st.clone(), st.clone(), st.clone()
+    g.rnn_update(*args, 0, W, eager)
+    stream = torch.cuda.Stream()
+    stream.wait_stream(torch.cuda.current_stream())
+    captured = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(captured, stream=stream):
+        g.rnn_update(*args, 0, W, graph)
+    for k in range(3):
+        if k:
+            g.rnn_update(*args, 0, W, eager)
+        g.rnn_update(*args, 0, W, fixed, noalloc=True)
+        torch.cuda.synchronize()
+        captured.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(fixed, eager) and torch.equal(graph, eager), f"update {k}"
+    assert not torch.equal(eager, st) and g.status() == 0
+    g.close()
 
 
 def _check_tiles(case):
