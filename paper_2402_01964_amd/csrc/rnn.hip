@@ -2032,8 +2032,8 @@ static int rnn_update(nlb_table *h, const int32_t *src, const int32_t *dst, cons
     p.o_vec = p.srb % 16 == 0;
 
     ResolveParams rp = {src, dst, n, h->num_nodes, wk.winner, h->status, count, 0,
-                        (const __bf16 *)wts->w_ih, (const __bf16 *)wts->w_hh, (u32x4 *)wk.wpack, p.d, p.kx, p.kd, p.kx / 32, (p.kx + p.kd) / 32,
-                        (uint32_t)(wpack_bytes / 16)};
+                        (const __bf16 *)wts->w_ih, (const __bf16 *)wts->w_hh, (u32x4 *)wk.wpack, p.d, p.kx, p.kd,
+                        p.kx / 32, (p.kx + p.kd) / 32, (uint32_t)(wpack_bytes / 16)};
     // (the weight pack by workgroups of its own: one piece per thread)
     const uint32_t rt = n >= kMergeLarge ? 1024u : n >= kMergeMid ? 512u : 256u;
     rp.link_blocks = (n + rt - 1u) / rt;
