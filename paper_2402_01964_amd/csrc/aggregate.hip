@@ -2226,7 +2226,8 @@ __global__ __launch_bounds__(kRowThreads) __attribute__((amdgpu_waves_per_eu(2, 
 // them, with the slots and with widths that cut its pieces of 8 values.
 // 20 slots, fp32 node rows of 4 and link rows of 4 values, 600 queries: 17.0 us
 // tiled, 19.3 in groups; 5 slots, rows of 20 and 30, 100 time columns, two heads,
-// 300 queries: 13.7 and 17.1; but rows of 100 and 172, 10 slots: 21.0 and 16.1.
+// 300 queries: 13.7 and 17.1; but rows of 100 and 172, 10 slots, 600 queries: 24.6
+// and 16.1.
 // The limits, by kinds of rows and by heads, are fitted to 2900 launches of 8 to
 // 1100 queries, 1 to 48 slots and 42 shapes: the choice costs 1.2 % in the root
 // mean square, and 10 % where a launch of the most slots lies at the line.
